@@ -359,11 +359,11 @@ size_t resa_rectify_workspace_size(int32_t batch, int32_t num_kv_heads,
  * summaries, out and lse rows keep their contents, and its q_f / k_f / v_f
  * rows are not read.
  * Value range: any finite bf16 V gives a finite out. P . V runs on fp16
- * matrix cores with P in [0, 2^8]; V enters at its own scale (exact for
- * |v| in 2^-14 .. 65280, fp16 subnormal spacing 2^-24 below), and a head
- * dimension holding larger values is scaled by a power of two for the
- * whole call from the first tile that needs it (its smaller values then lose
- * the bits below 2^-24 of the scale, far below 2e-3 of the dimension's
+ * matrix cores with P in [0, 2^12]; V enters at its own scale (exact for
+ * |v| in 2^-14 .. 65280, fp16 subnormal spacing 2^-24 below). Where a range of
+ * keys holds larger values, the workgroups that read it repeat their pass
+ * with each head dimension scaled by a power of two (the dimension's smaller
+ * values then lose the bits below 2^-24 of the scale, far below 2e-3 of its
  * largest magnitude).
  * Errors: RESA_ERR_INVALID_ARG for the ranges above or misaligned pointers,
  * RESA_ERR_WORKSPACE when a needed workspace is missing or too small.

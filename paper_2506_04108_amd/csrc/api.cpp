@@ -197,10 +197,10 @@ struct RectifyLayout {
 };
 
 RectifyLayout rectify_layout(int32_t batch, int32_t kv_heads, int32_t group, int32_t f,
-                             int32_t max_seq_len) {
+                             int32_t max_seq_len, bool masked) {
   RectifyLayout r;
   r.nq = resa::rectify_num_qblocks(group, f);
-  r.chunk = resa::rectify_chunk(batch, kv_heads, r.nq, max_seq_len);
+  r.chunk = resa::rectify_chunk(batch, kv_heads, group * f, max_seq_len, masked);
   r.splits = (max_seq_len + r.chunk - 1) / r.chunk;
   if (r.splits < 1) r.splits = 1;
   const size_t groups = (size_t)batch * kv_heads;
@@ -683,8 +683,7 @@ size_t resa_rectify_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t 
   // workspace sized once serves every shorter call (the layout of a call is
   // never larger: its offsets grow with its own split count).
   const int32_t group = num_q_heads / num_kv_heads;
-  const int32_t nq = resa::rectify_num_qblocks(group, f);
-  const int32_t most = resa::rectify_max_splits(batch, num_kv_heads, nq, max_seq_len);
+  const int32_t most = resa::rectify_max_splits(batch, num_kv_heads, group * f, max_seq_len);
   if (most == 1) return 0;  // every such call has one split, written to out / lse directly
   const size_t groups = (size_t)batch * num_kv_heads;
   const size_t rows = (size_t)group * f;
@@ -713,7 +712,7 @@ int resa_dense_rectify(const resa_kv_cache_t* c, const void* q_f, const void* k_
     return fail(RESA_ERR_INVALID_ARG, "max_seq_len %d outside [f = %d, capacity %d]", max_seq_len,
                 f, c->capacity);
   if (!std::isfinite(sm_scale)) return fail(RESA_ERR_INVALID_ARG, "sm_scale is not finite");
-  const RectifyLayout lay = rectify_layout(c->batch, c->num_kv_heads, group, f, max_seq_len);
+  const RectifyLayout lay = rectify_layout(c->batch, c->num_kv_heads, group, f, max_seq_len, seq_mask != nullptr);
   if (lay.total > 0 && (workspace == nullptr || workspace_bytes < lay.total))
     return fail(RESA_ERR_WORKSPACE, "rectify workspace needs %zu bytes, got %zu", lay.total,
                 workspace == nullptr ? (size_t)0 : workspace_bytes);
@@ -732,6 +731,7 @@ int resa_dense_rectify(const resa_kv_cache_t* c, const void* q_f, const void* k_
   a.max_seq_len = max_seq_len;
   a.chunk = lay.chunk;
   a.num_splits = lay.splits;
+  a.num_qblocks = lay.nq;
   a.scale_log2 = sm_scale * 1.4426950408889634f;
   a.out = out;
   a.lse = lse;

@@ -116,6 +116,7 @@ struct RectifyArgs {
   int32_t max_seq_len;
   int32_t chunk;               // keys per split
   int32_t num_splits;          // ceil(max_seq_len / chunk)
+  int32_t num_qblocks;         // query blocks per group
   float scale_log2;
   float* out;                  // [B, Hq, f, D]
   float* lse;                  // [B, Hq, f] or null
@@ -149,9 +150,9 @@ int32_t step_blocks_per_range(int32_t batch, int32_t kv_heads, int32_t max_block
 int32_t step_hist_words(int32_t batch, int32_t kv_heads, int32_t max_blocks_seq);
 int32_t step_max_blocks();
 int32_t rectify_num_qblocks(int32_t group, int32_t f);
-int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t nqblk, int32_t max_seq_len);
+int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked);
 // An upper bound on the key splits of any call with lengths up to
 // max_seq_len, non-decreasing in max_seq_len (workspace sizing).
-int32_t rectify_max_splits(int32_t batch, int32_t kv_heads, int32_t nqblk, int32_t max_seq_len);
+int32_t rectify_max_splits(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len);
 
 }  // namespace resa
