@@ -300,17 +300,6 @@ __device__ void merge_tail(const DecodeArgs& a, size_t grp, int S, int own, size
   }
 }
 
-// Wave-wide maximum and sum (every lane active; every lane gets the result):
-// the 16 lanes of each row by DPP, then the rows by lane swaps.
-__device__ __forceinline__ float wave_max_f(float x) {
-  x = fmaxf(x, dpp<kDppXor1>(x));
-  x = fmaxf(x, dpp<kDppXor2>(x));
-  x = fmaxf(x, dpp<kDppHalfMirror>(x));
-  x = fmaxf(x, dpp<kDppMirror>(x));
-  return max_xor32(max_xor16(x));
-}
-__device__ __forceinline__ float wave_sum_f(float x) { return sum_xor32(sum_xor16(row16_sum(x))); }
-
 // Alg. 2, "Combine", for one query head h of the group, by one of the G
 // merging workgroups of a group with many splits (each takes one head, so
 // each loads 1 / G of the partials). Thread i < S forms split i's weight

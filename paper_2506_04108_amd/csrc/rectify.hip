@@ -169,26 +169,64 @@ __device__ __forceinline__ f32x16_t mfma32(f16x8_t a, f16x8_t b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
-// Writes the re-encoded rows k_f, v_f over cache rows [L - f, L).
-// Grid (ceil(f / 16), batch * kv_heads): each workgroup copies 16 rows.
+// Writes the re-encoded rows k_f, v_f over cache rows [L - f, L) and, with
+// `refresh`, re-summarises the blocks they touch (Eq. 3), one wave per block:
+// lane (r, c) with r = lane / 16 and c = lane % 16 takes dims [8c, 8c + 8) of
+// rows r, r + 4, ... of the block, from k_f where the row is rewritten and
+// from the cache below the window. One launch in place of a copy and a
+// summary pass over the same rows (64K, f = 32: 4.0 + 3.8 us of kernel time
+// and a launch gap; 8K prompts, which it reads once instead of twice: 82 + 37
+// us). Grid (ceil(blocks / 4), batch * kv_heads), blocks <= ceil(f / b) + 1.
+template <int BS>
 __global__ __launch_bounds__(256) void k_rectify_rows(RectifyArgs a) {
-  const int grp = blockIdx.y;
-  const int bb = grp / a.c.kv_heads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int grp = blockIdx.y, bb = grp / a.c.kv_heads, hk = grp % a.c.kv_heads;
   if (a.seq_mask != nullptr && a.seq_mask[bb] == 0) return;
   const int L = a.seq_lens[bb];
-  if (L < a.f || L > a.c.capacity) return;
-  uint16_t* k = const_cast<uint16_t*>(a.c.k);
-  uint16_t* v = const_cast<uint16_t*>(a.c.v);
-  const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s < a.f * 16) {
-    const int row = s >> 4, part = s & 15;
-    const size_t src = ((size_t)grp * a.f + row) * kHeadDim + part * 8;
-    const int64_t kr = kv_row(a.c, bb, grp % a.c.kv_heads, L - a.f + row);
-    if (kr >= 0) {
-      const size_t dst = (size_t)kr * kHeadDim + part * 8;
-      st16(k + dst, ld16(a.k_f + src));
-      st16(v + dst, ld16(a.v_f + src));
+  if (L < a.f) return;
+  const int m = (L - a.f) / BS + blockIdx.x * 4 + wave;
+  if (m >= min((L + BS - 1) / BS, a.c.max_blocks)) return;
+  // A length past the capacity rewrites no row.
+  const int first = L <= a.c.capacity ? L - a.f : L;
+  const int64_t row0 = kv_row(a.c, bb, hk, m * BS);  // a block never straddles pages
+  if (row0 < 0) return;
+  const int r = lane >> 4, col = (lane & 15) * 8;
+  uint16_t* kb = const_cast<uint16_t*>(a.c.k) + (size_t)row0 * kHeadDim + col;
+  uint16_t* vb = const_cast<uint16_t*>(a.c.v) + (size_t)row0 * kHeadDim + col;
+  const uint16_t* kf = a.k_f + (size_t)grp * a.f * kHeadDim + col;
+  const uint16_t* vf = a.v_f + (size_t)grp * a.f * kHeadDim + col;
+  U4 rows[BS / 4];
+#pragma unroll
+  for (int i = 0; i < BS / 4; ++i) {
+    const int t = m * BS + r + 4 * i;
+    rows[i] = U4{0, 0, 0, 0};
+    if (t < L) {
+      if (t >= first)
+        rows[i] = ld16(kf + (size_t)(t - first) * kHeadDim);
+      else if (a.refresh)
+        rows[i] = ld16(kb + (size_t)(r + 4 * i) * kHeadDim);
     }
+  }
+#pragma unroll
+  for (int i = 0; i < BS / 4; ++i) {
+    const int t = m * BS + r + 4 * i;
+    if (t < L && t >= first) {
+      const U4 v = ld16(vf + (size_t)(t - first) * kHeadDim);
+      st16(kb + (size_t)(r + 4 * i) * kHeadDim, rows[i]);
+      st16(vb + (size_t)(r + 4 * i) * kHeadDim, v);
+    }
+  }
+  if (a.refresh) {
+    float mn[8], mx[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      mn[j] = __builtin_inff();
+      mx[j] = -__builtin_inff();
+    }
+#pragma unroll
+    for (int i = 0; i < BS / 4; ++i)
+      if (m * BS + r + 4 * i < L) fold_minmax(rows[i], mn, mx);
+    store_summary(a.c, (size_t)grp, m, r, col, mn, mx);
   }
 }
 
@@ -638,28 +676,78 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   }
 }
 
-// Log-sum-exp merge of the splits (Alg. 2, "Combine") spread over many
-// workgroups: each takes kCombineRows query rows of one group.
-constexpr int kCombineRows = 8;
-
+// Log-sum-exp merge of the splits (Alg. 2, "Combine"): kPerRow waves take one
+// query row, each a share of its splits (wave w splits w, w + kPerRow, ...).
+// Lane i holds dims 2i, 2i + 1 of the row, so a split's partial is one
+// 512-byte load of the wave; a wave takes 64 splits at a time, whose lse sit
+// one per lane: their weights are formed by all lanes at once and broadcast
+// one by one, with the partial loads of 16 splits in flight. One wave per row
+// where the splits are few (up to 16) and rows many; four otherwise.
+template <int kPerRow>
 __global__ __launch_bounds__(256) void k_rectify_combine(RectifyArgs a) {
-  __shared__ float s_w[kMaxRectSplits * kCombineRows];
-  __shared__ f4_t s_red[256];
-  const int grp = blockIdx.y;
-  const int bb = grp / a.c.kv_heads, hk = grp % a.c.kv_heads;
+  constexpr int kRows = 4 / kPerRow;   // query rows per workgroup
+  __shared__ f2_t s_acc[4][64];
+  __shared__ float s_m[4], s_l[4];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = blockIdx.y, bb = grp / a.c.kv_heads, hk = grp % a.c.kv_heads;
   if (a.seq_mask != nullptr && a.seq_mask[bb] == 0) return;
   const int G = a.group, f = a.f, R = G * f, S = a.num_splits;
-  const int rho0 = blockIdx.x * kCombineRows;
-  const int rows = min(kCombineRows, R - rho0);
-  if (rows <= 0) return;
-  auto out_index = [&](int r) {
-    const int rho = rho0 + r;
-    return ((size_t)bb * a.q_heads + (size_t)hk * G + rho % G) * f + rho / G;
-  };
-  merge_splits<false>(a.part_o + ((size_t)grp * S * R + rho0) * kHeadDim, (size_t)R * kHeadDim,
-               a.part_lse + (size_t)grp * S * R + rho0, (size_t)R, S, rows, s_w, s_red,
-               [&](int r) { return a.out + out_index(r) * kHeadDim; },
-               [&](int r, float v) { if (a.lse) a.lse[out_index(r)] = v; });
+  const int rho = blockIdx.x * kRows + wave / kPerRow, part = wave % kPerRow;
+  const float ninf = -__builtin_inff();
+  const bool live = rho < R;
+  const float* pl = a.part_lse + (size_t)grp * S * R + rho;
+  const float* po = a.part_o + ((size_t)grp * S * R + rho) * kHeadDim + 2 * lane;
+  const size_t stride = (size_t)R * kHeadDim;
+  float m = ninf, l = 0.f;
+  f2_t acc = {0.f, 0.f};
+  const int n = live ? (S - part + kPerRow - 1) / kPerRow : 0;  // this wave's splits
+  for (int b = 0; b < n; b += 64) {
+    const int cnt = min(64, n - b);
+    const float x = lane < cnt ? pl[(size_t)((b + lane) * kPerRow + part) * R] : ninf;
+    const float mn = fmaxf(m, wave_max_f(x));
+    const float e = x == ninf ? 0.f : fast_exp2(x - mn);
+    const float alpha = m == ninf ? 0.f : fast_exp2(m - mn);
+    l = fmaf(l, alpha, wave_sum_f(e));
+    acc *= alpha;
+    m = mn;
+    for (int q = 0; q < cnt; q += 16) {
+      f2_t p[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        p[u] = f2_t{0.f, 0.f};
+        if (q + u < cnt) p[u] = *reinterpret_cast<const f2_t*>(po + (size_t)((b + q + u) * kPerRow + part) * stride);
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        acc += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, e), (q + u) & 63)) * p[u];
+    }
+  }
+  if constexpr (kPerRow > 1) {
+    s_acc[wave][lane] = acc;
+    if (lane == 0) {
+      s_m[wave] = m;
+      s_l[wave] = l;
+    }
+    lds_sync();
+    if (part != 0) return;
+    float mx = m;
+#pragma unroll
+    for (int w = 1; w < kPerRow; ++w) mx = fmaxf(mx, s_m[wave + w]);
+    const float f0 = m == ninf ? 0.f : fast_exp2(m - mx);
+    l *= f0;
+    acc *= f0;
+#pragma unroll
+    for (int w = 1; w < kPerRow; ++w) {
+      const float mw = s_m[wave + w], fw = mw == ninf ? 0.f : fast_exp2(mw - mx);
+      l = fmaf(s_l[wave + w], fw, l);
+      acc += fw * s_acc[wave + w][lane];
+    }
+    m = mx;
+  }
+  if (!live) return;
+  const size_t oi = ((size_t)bb * a.q_heads + (size_t)hk * G + rho % G) * f + rho / G;
+  *reinterpret_cast<f2_t*>(a.out + oi * kHeadDim + 2 * lane) = acc * (l > 0.f ? 1.f / l : 0.f);
+  if (lane == 0 && a.lse) a.lse[oi] = l > 0.f ? (m + fast_log2(l)) * kLn2 : ninf;
 }
 
 }  // namespace
@@ -730,14 +818,16 @@ int32_t rectify_max_splits(int32_t batch, int32_t kv_heads, int32_t rows, int32_
 }
 
 hipError_t launch_rectify(const RectifyArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(k_rectify_rows, dim3((a.f + 15) / 16, a.c.batch * a.c.kv_heads), dim3(256), 0,
-                     stream, a);
+  const int nblk = (a.f + a.c.block_size - 1) / a.c.block_size + 1;  // blocks rows [L - f, L) can touch
+  const dim3 rows_grid((nblk + 3) / 4, a.c.batch * a.c.kv_heads);
+  switch (a.c.block_size) {
+    case 16: hipLaunchKernelGGL(k_rectify_rows<16>, rows_grid, dim3(256), 0, stream, a); break;
+    case 32: hipLaunchKernelGGL(k_rectify_rows<32>, rows_grid, dim3(256), 0, stream, a); break;
+    case 64: hipLaunchKernelGGL(k_rectify_rows<64>, rows_grid, dim3(256), 0, stream, a); break;
+    default: return hipErrorInvalidValue;
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.refresh) {
-    e = launch_summarize_tail(a.c, a.seq_lens, a.f, a.seq_mask, stream);
-    if (e != hipSuccess) return e;
-  }
   const int groups = a.c.batch * a.c.kv_heads;
   const dim3 grid(a.num_splits * rectify_items(groups, a.num_qblocks) * groups);
   const bool paged = a.c.table != nullptr;
@@ -758,9 +848,11 @@ hipError_t launch_rectify(const RectifyArgs& a, hipStream_t stream) {
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.num_splits == 1) return hipSuccess;  // the attention kernel wrote out / lse
-  const int32_t rows = a.group * a.f;
-  hipLaunchKernelGGL(k_rectify_combine, dim3((rows + kCombineRows - 1) / kCombineRows,
-                     a.c.batch * a.c.kv_heads), dim3(256), 0, stream, a);
+  const int rows = a.group * a.f;
+  if (a.num_splits <= 16)
+    hipLaunchKernelGGL(k_rectify_combine<1>, dim3((rows + 3) / 4, groups), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(k_rectify_combine<4>, dim3(rows, groups), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "resa.h"
+#include "resa_device.h"
 
 namespace resa {
 
@@ -41,6 +42,38 @@ __device__ __forceinline__ int64_t kv_row(const CacheArgs& c, int bb, int hk, in
   const int page = c.table[(size_t)bb * c.max_blocks + m];
   if ((unsigned)page >= (unsigned)c.num_pages) return -1;
   return ((int64_t)page * c.kv_heads + hk) * c.block_size + (t - (m << c.log2_block));
+}
+
+// Eq. 3 over one wave: lane (r, c) has folded dims [8c, 8c + 8) of rows r,
+// r + 4, ... of block m into mn / mx (fp32 bit patterns of bf16 values, so
+// exact); the four row groups are combined across lanes and lanes 0 .. 15
+// store the block's kmin / kmax row. Every lane must be active.
+__device__ __forceinline__ void fold_minmax(const U4& x, float (&mn)[8], float (&mx)[8]) {
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    mn[2 * j] = fminf(mn[2 * j], bf_lo(w[j]));
+    mn[2 * j + 1] = fminf(mn[2 * j + 1], bf_hi(w[j]));
+    mx[2 * j] = fmaxf(mx[2 * j], bf_lo(w[j]));
+    mx[2 * j + 1] = fmaxf(mx[2 * j + 1], bf_hi(w[j]));
+  }
+}
+__device__ __forceinline__ void store_summary(const CacheArgs& c, size_t grp, int m, int r, int col,
+                                              float (&mn)[8], float (&mx)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    mn[j] = fminf(mn[j], __shfl_xor(mn[j], 16));
+    mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 16));
+    mn[j] = fminf(mn[j], __shfl_xor(mn[j], 32));
+    mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32));
+  }
+  if (r == 0) {
+    const size_t so = (grp * c.max_blocks + m) * kHeadDim + col;
+    st16(c.kmin + so, U4{pack_exact(mn[0], mn[1]), pack_exact(mn[2], mn[3]),
+                         pack_exact(mn[4], mn[5]), pack_exact(mn[6], mn[7])});
+    st16(c.kmax + so, U4{pack_exact(mx[0], mx[1]), pack_exact(mx[2], mx[3]),
+                         pack_exact(mx[4], mx[5]), pack_exact(mx[6], mx[7])});
+  }
 }
 
 struct SelectArgs {
@@ -129,8 +162,6 @@ struct RectifyArgs {
 // Launchers: enqueue on `stream`; return the hipError_t of the launch.
 hipError_t launch_summarize(const CacheArgs& c, const int32_t* seq_lens, int32_t blk_begin,
                             int32_t blk_end, hipStream_t stream);
-hipError_t launch_summarize_tail(const CacheArgs& c, const int32_t* seq_lens, int32_t f,
-                                 const int32_t* seq_mask, hipStream_t stream);
 hipError_t launch_append(const CacheArgs& c, const uint16_t* k_new, const uint16_t* v_new,
                          int32_t* seq_lens, hipStream_t stream);
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream);

@@ -9,24 +9,13 @@ namespace {
 // One wave summarises one block: lane (r, c) with r = lane / 16 and
 // c = lane % 16 reads dims [8c, 8c + 8) of rows r, r + 4, ... of the block,
 // so each wave-wide load covers four whole 256-byte rows (1 KiB contiguous).
-//
-// With rel_f > 0 the range is per sequence: blocks floor((L - rel_f) / b) ..
-// M - 1, i.e. every block holding one of the last rel_f rows (rectify
-// refresh); a sequence whose seq_mask entry is 0 is skipped (seq_mask may be
-// null: every sequence).
 template <int BS>
 __global__ __launch_bounds__(256) void k_summarize(CacheArgs c, const int32_t* __restrict__ seq_lens,
-                                                   int32_t blk_begin, int32_t blk_end, int32_t rel_f,
-                                                   const int32_t* __restrict__ seq_mask) {
+                                                   int32_t blk_begin, int32_t blk_end) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int hk = blockIdx.y, bb = blockIdx.z;
-  if (seq_mask != nullptr && seq_mask[bb] == 0) return;
   const int L = seq_lens[bb];
-  if (rel_f > 0) {
-    if (L < rel_f) return;
-    blk_begin = (L - rel_f) / BS;
-  }
   const int m = blk_begin + blockIdx.x * 4 + wave;
   const int M = (L + BS - 1) / BS;
   int end = blk_end < 0 ? M : min(blk_end, M);
@@ -48,33 +37,9 @@ __global__ __launch_bounds__(256) void k_summarize(CacheArgs c, const int32_t* _
 #pragma unroll
   for (int i = 0; i < BS / 4; ++i) rows[i] = ld16(kb + (size_t)(r + 4 * i) * kHeadDim);
 #pragma unroll
-  for (int i = 0; i < BS / 4; ++i) {
-    if (m * BS + r + 4 * i < L) {
-      const uint32_t w[4] = {rows[i].x, rows[i].y, rows[i].z, rows[i].w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        mn[2 * j] = fminf(mn[2 * j], bf_lo(w[j]));
-        mn[2 * j + 1] = fminf(mn[2 * j + 1], bf_hi(w[j]));
-        mx[2 * j] = fmaxf(mx[2 * j], bf_lo(w[j]));
-        mx[2 * j + 1] = fmaxf(mx[2 * j + 1], bf_hi(w[j]));
-      }
-    }
-  }
-  // Combine the four row groups (lanes c, c+16, c+32, c+48 hold the same dims).
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    mn[j] = fminf(mn[j], __shfl_xor(mn[j], 16));
-    mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 16));
-    mn[j] = fminf(mn[j], __shfl_xor(mn[j], 32));
-    mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], 32));
-  }
-  if (r == 0) {
-    const size_t so = (grp * c.max_blocks + m) * kHeadDim + col;
-    st16(c.kmin + so, U4{pack_exact(mn[0], mn[1]), pack_exact(mn[2], mn[3]),
-                         pack_exact(mn[4], mn[5]), pack_exact(mn[6], mn[7])});
-    st16(c.kmax + so, U4{pack_exact(mx[0], mx[1]), pack_exact(mx[2], mx[3]),
-                         pack_exact(mx[4], mx[5]), pack_exact(mx[6], mx[7])});
-  }
+  for (int i = 0; i < BS / 4; ++i)
+    if (m * BS + r + 4 * i < L) fold_minmax(rows[i], mn, mx);
+  store_summary(c, grp, m, r, col, mn, mx);
 }
 
 // One workgroup per sequence; wave w handles kv heads w, w + 4, ...
@@ -127,31 +92,18 @@ __global__ void k_clear(uint8_t* p, size_t bytes) {
 
 }  // namespace
 
-static hipError_t summarize_grid(const CacheArgs& c, const int32_t* seq_lens, int32_t blk_begin,
-                                 int32_t blk_end, int32_t rel_f, const int32_t* seq_mask, int32_t nblk,
-                                 hipStream_t stream) {
+hipError_t launch_summarize(const CacheArgs& c, const int32_t* seq_lens, int32_t blk_begin,
+                            int32_t blk_end, hipStream_t stream) {
+  const int32_t nblk = (blk_end < 0 ? c.max_blocks : blk_end) - blk_begin;
   if (nblk <= 0) return hipSuccess;
   dim3 grid((nblk + 3) / 4, c.kv_heads, c.batch);
   switch (c.block_size) {
-    case 16: hipLaunchKernelGGL(k_summarize<16>, grid, dim3(256), 0, stream, c, seq_lens, blk_begin, blk_end, rel_f, seq_mask); break;
-    case 32: hipLaunchKernelGGL(k_summarize<32>, grid, dim3(256), 0, stream, c, seq_lens, blk_begin, blk_end, rel_f, seq_mask); break;
-    case 64: hipLaunchKernelGGL(k_summarize<64>, grid, dim3(256), 0, stream, c, seq_lens, blk_begin, blk_end, rel_f, seq_mask); break;
+    case 16: hipLaunchKernelGGL(k_summarize<16>, grid, dim3(256), 0, stream, c, seq_lens, blk_begin, blk_end); break;
+    case 32: hipLaunchKernelGGL(k_summarize<32>, grid, dim3(256), 0, stream, c, seq_lens, blk_begin, blk_end); break;
+    case 64: hipLaunchKernelGGL(k_summarize<64>, grid, dim3(256), 0, stream, c, seq_lens, blk_begin, blk_end); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-hipError_t launch_summarize(const CacheArgs& c, const int32_t* seq_lens, int32_t blk_begin,
-                            int32_t blk_end, hipStream_t stream) {
-  const int32_t last = blk_end < 0 ? c.max_blocks : blk_end;
-  return summarize_grid(c, seq_lens, blk_begin, blk_end, 0, nullptr, last - blk_begin, stream);
-}
-
-hipError_t launch_summarize_tail(const CacheArgs& c, const int32_t* seq_lens, int32_t f,
-                                 const int32_t* seq_mask, hipStream_t stream) {
-  // Rows [L - f, L) touch at most ceil(f / b) + 1 blocks.
-  const int32_t nblk = (f + c.block_size - 1) / c.block_size + 1;
-  return summarize_grid(c, seq_lens, 0, -1, f, seq_mask, nblk, stream);
 }
 
 hipError_t launch_append(const CacheArgs& c, const uint16_t* k_new, const uint16_t* v_new,
