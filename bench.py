@@ -5,7 +5,7 @@ append the token's K/V (online block-summary update), select blocks (pooled
 query, Quest score, top-n) and run block-sparse flash-decoding; every f-th
 step of a layer also runs the dense rectification of its last f rows. By
 default the step is resa_append_select then resa_sparse_decode (--mode two);
---mode step runs one launch of resa_decode_step, --mode three (--separate)
+--mode step runs resa_decode_step, --mode three (--separate)
 resa_append_kv, resa_select_blocks and resa_sparse_decode. The default
 workload is the 64K batch-8 decode loop (32 query / 8 kv heads, head_dim 128,
 block 16, sparsity 0.9 with a 2048-token minimum, f = 32, LogNormal(0, 0.5)
@@ -84,7 +84,7 @@ def parse():
     p.add_argument("--prefill", action="store_true",
                    help="time prefill (chunked and whole-prompt) through the rectification call")
     p.add_argument("--mode", choices=["step", "two", "three"], default="two",
-                   help="step: resa_decode_step (append + select + decode in one launch); "
+                   help="step: resa_decode_step (append + select + decode in one call); "
                         "two: resa_append_select then resa_sparse_decode; three: resa_append_kv, "
                         "resa_select_blocks, resa_sparse_decode")
     p.add_argument("--separate", dest="mode", action="store_const", const="three",
@@ -131,7 +131,8 @@ def describe(w, layers, dense):
 # kernel's HBM counter figures.
 KERNEL_SOURCES = {
     "k_decode": ["decode.hip", "decode_impl.h", "resa_device.h", "resa_internal.h"],
-    "k_step": ["step.hip", "select_impl.h", "decode_impl.h", "resa_device.h", "resa_internal.h"],
+    "k_select + k_decode": ["select.hip", "select_impl.h", "decode.hip", "decode_impl.h", "resa_device.h",
+                            "resa_internal.h"],
 }
 
 
@@ -532,7 +533,7 @@ def measure(args, w, dense: bool) -> dict:
     dec_key = "decode_alone" if "decode_alone" in phase_us else "decode"
     dec_roof = roof("k_decode", "sparse_decode", avg_bytes, phase_us[dec_key])
     if "step" in phase_us:
-        roofline = roof("k_step", "decode_step", avg_bytes + avg_sum, phase_us["step"])
+        roofline = roof("k_select + k_decode", "decode_step", avg_bytes + avg_sum, phase_us["step"])
     else:
         roofline = dec_roof
     ms_per_step = step_us / 1e3

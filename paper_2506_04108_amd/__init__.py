@@ -297,7 +297,7 @@ def decode_step(cache: KVCache, k_new: torch.Tensor, v_new: torch.Tensor, q: tor
                 num_sel: torch.Tensor | None = None, out: torch.Tensor | None = None,
                 lse: torch.Tensor | None = None, with_lse: bool = True,
                 workspace: Workspace | None = None, stream=None):
-    """One decode token (Alg. 1) in one launch: append (seq_lens incremented
+    """One decode token (Alg. 1) in one call: append (seq_lens incremented
     in place), Eq. 4-5 selection and Eq. 2 / Alg. 2 sparse decoding.
     ``max_seq_len`` bounds seq_lens before the call. Returns
     ``(block_idx, num_sel, out, lse)`` as :func:`append_select` and

@@ -14,19 +14,19 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libresa.so")
-SOURCES = ["api.cpp", "summarize.hip", "select.hip", "decode.hip", "step.hip", "rectify.hip",
+SOURCES = ["api.cpp", "summarize.hip", "select.hip", "decode.hip", "rectify.hip",
            "probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # Packed fp32 VALU instructions are kept out of the generated code.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# Per-source flags. The selection's top-n tail (select.hip, step.hip) and the
+# Per-source flags. The selection's top-n tail (select.hip) and the
 # decode's split ticket (decode.hip) take one-lane atomics whose results are
 # needed only later; the atomic optimizer would broadcast each result right
 # away, making the wave wait for the atomic and for every load issued before it.
 EXTRA = {src: ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
-         for src in ("select.hip", "step.hip", "decode.hip")}
+         for src in ("select.hip", "decode.hip")}
 COMMON = ["-O3", "-std=c++20", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
           "-Wno-unused-command-line-argument", "-I", os.path.join(HERE, "..", "include")]
 

@@ -6,7 +6,6 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
-#include <cstdlib>
 #include <mutex>
 #include <string>
 
@@ -166,26 +165,18 @@ DecodeLayout decode_layout(int32_t batch, int32_t kv_heads, int32_t group, int32
   return d;
 }
 
-// Workspace of resa_decode_step: claim counters and per-group ready flags,
-// then a selection workspace (score ranges of the step) and a decode
-// workspace.
+// Workspace of resa_decode_step: a status area (words 0 .. 63 and one word per
+// group, always zero), then a selection workspace and a decode workspace.
 struct StepLayout {
-  size_t queue, ready, sel, dec, total;
-  SelectLayout s;
+  size_t sel, dec, total;
   DecodeLayout d;
 };
 
 StepLayout step_layout(int32_t batch, int32_t kv_heads, int32_t group, int32_t sel_len,
                        int32_t block_size, int32_t splits) {
   StepLayout l;
-  const size_t groups = (size_t)batch * kv_heads;
-  const size_t mseq = ((size_t)sel_len + block_size - 1) / block_size;
-  l.queue = 0;
-  l.ready = 256;
-  l.sel = l.ready + round256(groups * 4);
-  l.s = select_layout_words(batch, kv_heads, mseq,
-                            (size_t)resa::step_hist_words(batch, kv_heads, (int32_t)mseq));
-  l.dec = l.sel + round256(l.s.total);
+  l.sel = 256 + round256((size_t)batch * kv_heads * 4);
+  l.dec = l.sel + round256(select_layout(batch, kv_heads, sel_len, block_size).total);
   l.d = decode_layout(batch, kv_heads, group, splits);
   l.total = l.dec + l.d.total;
   return l;
@@ -277,7 +268,7 @@ int select_common(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
                   const int32_t* seq_lens, int32_t sel_len, const resa_select_params_t* params,
                   int32_t* block_idx, int32_t* num_sel, int32_t n_cap, float* scores_out,
                   void* workspace, size_t workspace_bytes, const void* k_new, const void* v_new,
-                  void* stream, const char* what) {
+                  bool step, void* stream, const char* what) {
   int32_t group = 0;
   if (int e = check_heads(c, num_q_heads, &group)) return e;
   RESA_CHECK_PTR(q, 16);
@@ -323,6 +314,7 @@ int select_common(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
   a.hist = reinterpret_cast<uint32_t*>(ws + lay.hist);
   a.blocks_per_wg = resa::select_blocks_per_wg(c->batch, c->num_kv_heads, mseq);
   a.fused = mseq <= resa::select_fused_max_blocks() ? 1 : 0;
+  a.lists = step ? 1 : 0;
   a.k_new = static_cast<const uint16_t*>(k_new);
   a.v_new = static_cast<const uint16_t*>(v_new);
   a.lens_out = const_cast<int32_t*>(seq_lens);
@@ -349,7 +341,7 @@ int resa_select_blocks(const resa_kv_cache_t* c, const void* q, int32_t num_q_he
     return fail(RESA_ERR_INVALID_ARG, "max_seq_len %d outside [0, capacity %d]", max_seq_len,
                 c->capacity);
   return select_common(c, q, num_q_heads, seq_lens, max_seq_len, params, block_idx, num_sel, n_cap,
-                       scores_out, workspace, workspace_bytes, nullptr, nullptr, stream,
+                       scores_out, workspace, workspace_bytes, nullptr, nullptr, false, stream,
                        "resa_select_blocks launch");
 }
 
@@ -366,7 +358,7 @@ int resa_append_select(const resa_kv_cache_t* c, const void* k_new, const void* 
     return fail(RESA_ERR_CAPACITY, "cache full: max_seq_len %d, capacity %d", max_seq_len,
                 c->capacity);
   return select_common(c, q, num_q_heads, seq_lens, max_seq_len + 1, params, block_idx, num_sel,
-                       n_cap, scores_out, workspace, workspace_bytes, k_new, v_new, stream,
+                       n_cap, scores_out, workspace, workspace_bytes, k_new, v_new, false, stream,
                        "resa_append_select launch");
 }
 
@@ -449,8 +441,6 @@ int decode_launch(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
   a.flags = reinterpret_cast<uint64_t*>(ws + lay.flags);
   a.part_lse = reinterpret_cast<float*>(ws + lay.lse);
   a.part_o = reinterpret_cast<float*>(ws + lay.o);
-  a.k_new = nullptr;
-  a.v_new = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (clear_counters) {
     hipError_t e = resa::launch_clear(ws + lay.counters, lay.lse - lay.counters, st);
@@ -590,9 +580,9 @@ int resa_decode_step(const resa_kv_cache_t* c, const void* k_new, const void* v_
   if (!std::isfinite(sm_scale)) return fail(RESA_ERR_INVALID_ARG, "sm_scale is not finite");
   const int32_t sel_len = max_seq_len + 1;
   const int32_t mseq = (sel_len + c->block_size - 1) / c->block_size;
-  if (mseq > resa::step_max_blocks())
-    return fail(RESA_ERR_UNSUPPORTED, "%d blocks per sequence exceed the fused step's %d", mseq,
-                resa::step_max_blocks());
+  if (mseq > resa::select_fused_max_blocks())
+    return fail(RESA_ERR_UNSUPPORTED, "%d blocks per sequence exceed the decode step's %d", mseq,
+                resa::select_fused_max_blocks());
   const int32_t need = resa::count_selected(mseq, keep, params->min_blocks, params->n_local);
   if (n_cap < need)
     return fail(RESA_ERR_CAPACITY, "n_cap %d < %d blocks selectable at %d tokens", n_cap, need,
@@ -606,73 +596,12 @@ int resa_decode_step(const resa_kv_cache_t* c, const void* k_new, const void* v_
                 workspace == nullptr ? (size_t)0 : workspace_bytes);
   if (!aligned(workspace, 16)) return fail(RESA_ERR_INVALID_ARG, "workspace is not 16-byte aligned");
   char* ws = static_cast<char*>(workspace);
-  char* wsel = ws + lay.sel;
-  char* wdec = ws + lay.dec;
-  const int64_t groups = (int64_t)c->batch * c->num_kv_heads;
-  resa::StepArgs a;
-  resa::SelectArgs& sa = a.s;
-  sa.c = cache_args(c);
-  sa.q = static_cast<const uint16_t*>(q);
-  sa.q_heads = num_q_heads;
-  sa.group = group;
-  sa.seq_lens = seq_lens;
-  sa.max_blocks_seq = mseq;
-  sa.keep_ppm = keep;
-  sa.min_blocks = params->min_blocks;
-  sa.n_local = params->n_local;
-  sa.keys = reinterpret_cast<uint32_t*>(wsel + lay.s.keys);
-  sa.score_stride = (mseq + 3) & ~3;
-  sa.scores_out = nullptr;
-  sa.block_idx = block_idx;
-  sa.num_sel = num_sel;
-  sa.n_cap = n_cap;
-  sa.counters = reinterpret_cast<uint32_t*>(wsel + lay.s.counters);
-  sa.hist = reinterpret_cast<uint32_t*>(wsel + lay.s.hist);
-  sa.blocks_per_wg = resa::step_blocks_per_range(c->batch, c->num_kv_heads, mseq);
-  sa.fused = 1;
-  sa.k_new = static_cast<const uint16_t*>(k_new);
-  sa.v_new = static_cast<const uint16_t*>(v_new);
-  sa.lens_out = seq_lens;
-  sa.seq_counters = reinterpret_cast<uint32_t*>(wsel + lay.s.seq_counters);
-  sa.window = reinterpret_cast<uint32_t*>(wsel + lay.s.window);
-  sa.stats = reinterpret_cast<uint32_t*>(wsel + lay.s.stats);
-  sa.above_bits = reinterpret_cast<uint32_t*>(wsel + lay.s.above_bits);
-  sa.bits_stride = (int32_t)bits_stride(mseq);
-  sa.win_keys = reinterpret_cast<uint64_t*>(wsel + lay.s.win_keys);
-  resa::DecodeArgs& d = a.d;
-  d.c = sa.c;
-  d.q = sa.q;
-  d.q_heads = num_q_heads;
-  d.group = group;
-  d.seq_lens = seq_lens;
-  d.block_idx = block_idx;
-  d.num_sel = num_sel;
-  d.n_cap = n_cap;
-  d.num_splits = splits;
-  d.scale_log2 = sm_scale * 1.4426950408889634f;
-  d.out = out;
-  d.lse = lse;
-  d.counters = reinterpret_cast<uint32_t*>(wdec + lay.d.counters);
-  d.epochs = reinterpret_cast<uint32_t*>(wdec + lay.d.epochs);
-  d.flags = reinterpret_cast<uint64_t*>(wdec + lay.d.flags);
-  d.part_lse = reinterpret_cast<float*>(wdec + lay.d.lse);
-  d.part_o = reinterpret_cast<float*>(wdec + lay.d.o);
-  d.k_new = sa.k_new;
-  d.v_new = sa.v_new;
-  a.queue = reinterpret_cast<uint32_t*>(ws + lay.queue);
-  a.ready = reinterpret_cast<uint32_t*>(ws + lay.ready);
-  a.nranges = (mseq + sa.blocks_per_wg - 1) / sa.blocks_per_wg;
-  if (a.nranges < 1) a.nranges = 1;
-  a.score_items = (int32_t)(groups * a.nranges);
-  a.dec_items = (int32_t)(groups * splits);
-  // Bound of a decode split's wait for its group's selection (polls of about
-  // 128 cycles each, ~1 s): a guard a correct launch never reaches. Tests of
-  // the guard lower it through RESA_STEP_MAX_SPINS.
-  a.max_spins = 1u << 20;
-  if (const char* env = std::getenv("RESA_STEP_MAX_SPINS")) a.max_spins = (uint32_t)std::strtoul(env, nullptr, 10);
-  hipError_t e = resa::launch_step(a, static_cast<hipStream_t>(stream));
-  if (e != hipSuccess) return hip_fail(e, "resa_decode_step launch");
-  return ok();
+  // Every argument is checked: the two launches follow.
+  if (int e = select_common(c, q, num_q_heads, seq_lens, sel_len, params, block_idx, num_sel, n_cap, nullptr,
+                            ws + lay.sel, lay.dec - lay.sel, k_new, v_new, true, stream, "resa_decode_step launch"))
+    return e;
+  return decode_launch(c, q, num_q_heads, seq_lens, block_idx, num_sel, n_cap, group, splits, sm_scale, out, lse,
+                       ws + lay.dec, lay.d, false, stream, "resa_decode_step launch");
 }
 
 size_t resa_rectify_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t num_q_heads,

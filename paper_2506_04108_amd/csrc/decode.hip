@@ -18,8 +18,7 @@ constexpr int kDecodeDepth = 1;
 template <int G, int BS>
 __global__ __launch_bounds__(64 * kDecodeWaves) void k_decode(DecodeArgs a) {
   __shared__ DecodeLds<G, kDecodeWaves> lds;
-  decode_split<G, BS, kDecodeWaves, false, kDecodeDepth>(a, blockIdx.z, blockIdx.y, blockIdx.x, a.seq_lens,
-                                                         false, lds);
+  decode_split<G, BS, kDecodeWaves, kDecodeDepth>(a, blockIdx.z, blockIdx.y, blockIdx.x, lds);
 }
 
 template <int G>

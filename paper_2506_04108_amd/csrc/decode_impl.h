@@ -1,9 +1,8 @@
 // Group block-sparse flash-decoding (Eq. 2; App. A, Alg. 2) for gfx950.
 //
-// Device code shared by the decode kernel and the fused decode step. The
-// selected blocks of a (sequence, kv head) group are cut into 16-token chunks
-// and the chunks are dealt to num_splits splits one by one (split s takes
-// chunk slots s, s + S, ...); wave w of a split's workgroup of NW waves takes
+// Device code of the decode kernel. The selected blocks of a (sequence, kv
+// head) group are cut into 16-token chunks and the chunks are dealt to
+// num_splits splits one by one (split s takes chunk slots s, s + S, ...); wave w of a split's workgroup of NW waves takes
 // the split's slots w, w + NW, ..., with kDepth chunks' loads in flight per
 // wave while one is consumed.
 //
@@ -42,8 +41,7 @@ struct Chunk {
 // kp / vp (wave-uniform): non-temporal buffer loads over the chunk's 4 KB of
 // each, at the lane's offset loff (elements) into a row. The resource base
 // is a scalar sum and the offsets 32-bit (measured 0.3 – 0.7 us per launch
-// faster than 64-bit global addressing at 64K and 256K, and 1 – 2 us faster
-// in the persistent step kernel).
+// faster than 64-bit global addressing at 64K and 256K).
 __device__ __forceinline__ void load_chunk(Chunk& ch, const uint16_t* kp, const uint16_t* vp,
                                            const int (&krow)[4], int row0, int loff) {
   constexpr int kBytes = kChunk * kHeadDim * 2;
@@ -202,13 +200,13 @@ __device__ __forceinline__ void consume_chunk(const Chunk& ch, int t0, int r, in
 // are added through LDS.
 constexpr int kTailBatch = 16;    // partial loads per thread per round
 
-template <int G, int NT, bool kOpaque>
+template <int G, int NT>
 __device__ void merge_tail(const DecodeArgs& a, size_t grp, int S, int own, size_t ob,
                            const float* own_o, const float* own_l, float* s_lse, f4_t* s_red) {
   constexpr int U = G * (kHeadDim / 4);
   constexpr int T = U >= NT ? 1 : NT / U;
   constexpr int kLse = (kMaxSplits * G + NT - 1) / NT;
-  const int tid = tid_of<kOpaque>();
+  const int tid = threadIdx.x;
   const float ninf = -__builtin_inff();
   const float* pl = wave_uniform(a.part_lse + grp * S * (size_t)G);
   const float* po = wave_uniform(a.part_o + grp * S * (size_t)(G * kHeadDim));
@@ -379,17 +377,12 @@ __device__ void merge_head(const DecodeArgs& a, size_t grp, int S, int own, int 
 
 // LDS of one split: per-wave softmax states for the wave merge, the staged
 // chunk list, and the merge of the splits.
-// Row-group states kept for the merge of the waves: all four row groups of
-// each wave (RG = 4) or, for 8-wave workgroups, whose LDS is shared with the
-// selection, the two pairs left by one lane swap (RG = 2).
-template <int NW>
-constexpr int kRowGroups = NW <= 4 ? 4 : 2;
-
-// Entry e = w RG + r holds accumulator racc[w][r][h][:] and, per head h, its
+// Entry e = 4 w + r: the state of wave w's row group r. It
+// holds accumulator racc[w][r][h][:] and, per head h, its
 // softmax reference rm[h][e] and sum rl[h][e] (contiguous per head).
 template <int G, int NW>
 struct DecodeLds {
-  static constexpr int RG = kRowGroups<NW>;
+  static constexpr int RG = 4;  // row groups of a wave
   __attribute__((aligned(16))) float racc[NW][RG][G][kHeadDim];
   __attribute__((aligned(16))) float rm[G][NW * RG];
   __attribute__((aligned(16))) float rl[G][NW * RG];
@@ -410,38 +403,21 @@ constexpr uint32_t kFlagSpins = 1u << 22;
 // query head each (merge_head), instead of done by the last one alone.
 constexpr int kSpreadSplits = 16;
 
-template <bool kCoherent>
-__device__ __forceinline__ int ld_i32(const int32_t* p) {
-  if constexpr (kCoherent) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else return *p;
-}
-
-
 // Split `split` of group (bb, hk) by a workgroup of NW waves: wave w takes
-// chunks c0 + w, c0 + w + NW, ... of the split's range. The group's length
-// is lens[bb]; with `append` (the fused step) a sequence below capacity has
-// one more token, appended in the same launch at row lens[bb], whose row is
-// taken from a.k_new / a.v_new instead of the cache. kCoherent: the ids and
-// the count were written by another workgroup of the same launch (agent-scope
-// loads; also selects the opaque thread index of the persistent kernel).
-// Every workgroup of the group writes its partial (several splits) and the
-// last one to finish merges them; returns true in the workgroup that wrote
-// the group's output. `empty`: the split decodes no chunk (it still takes
-// part in the merge).
+// chunks w, w + NW, ... of the split. Every workgroup of the group writes its
+// partial (several splits) and the last one(s) to finish merge them.
 //
 // Start-up: the count, the length, the query rows and the first pass's ids
 // are all requested before anything waits for one of them (vector loads, so
 // one wait covers them), which leaves one memory round trip between the
 // kernel arguments and the first K / V loads.
-template <int G, int BS, int NW, bool kCoherent, int kDepth>
-__device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk, int split,
-                                             const int32_t* lens, bool append, DecodeLds<G, NW>& lds,
-                                             bool empty = false) {
+template <int G, int BS, int NW, int kDepth>
+__device__ __forceinline__ void decode_split(const DecodeArgs& a, int bb, int hk, int split, DecodeLds<G, NW>& lds) {
   constexpr int GP = Pad<G>::GP;
   constexpr int CPB = BS / kChunk;  // chunks per block
   constexpr int NT = 64 * NW;
   constexpr int kPer = kIdxBatch / NT;  // ids per thread per pass
-  const int tid = tid_of<kCoherent>();
+  const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = a.num_splits;
@@ -464,7 +440,7 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       const int i = tid + j * NT;
-      blkv[j] = i < lim ? ld_i32<kCoherent>(idx + slot_of(cb + i) / CPB) : -1;
+      blkv[j] = i < lim ? idx[slot_of(cb + i) / CPB] : -1;
     }
   };
   load_ids(0);
@@ -498,18 +474,15 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
   const float ninf = -__builtin_inff();
   // The count and the length are requested last: the first use of either
   // (a move into scalar registers) then waits for everything above at once.
-  const int n_raw = ld_i32<true>(a.num_sel + grp);
-  const int L0 = ld_i32<true>(lens + bb);
+  const int n_raw = __hip_atomic_load(a.num_sel + grp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int L = __hip_atomic_load(a.seq_lens + bb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // Calls of this group merged so far: tags this call's ready flags.
   // Requested with the count and the length (unconditionally: behind a
   // branch the compiler would move it into a scalar register, and so wait
   // for it, right there); nothing uses it before the tail.
   uint32_t epoch = __hip_atomic_load(a.epochs + grp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const bool app = append && L0 >= 0 && L0 < a.c.capacity;
-  const int L = app ? L0 + 1 : L0;
-  const int pos = app ? L0 : -1;
   const int M = min((L + BS - 1) / BS, a.c.max_blocks);
-  const int n = empty ? 0 : max(0, min(n_raw, a.n_cap));
+  const int n = max(0, min(n_raw, a.n_cap));
   const int C = n * CPB;
   const int valid = count_below(C);
 
@@ -571,24 +544,6 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
     // and is masked out entirely, and nothing is loaded past the pass. The
     // scheduling barriers keep the refills ahead of the compute.
     auto tok = [&](int cc) -> int { return cc < ce ? __builtin_amdgcn_readfirstlane(lds.tok[cc - cb]) : -1; };
-    // The chunk holding token pos (appended in this launch) takes that row
-    // from k_new / v_new: lane row r + 4 iv of the chunk is K slot iv ^ rperm
-    // and V slot iv.
-    auto patch = [&](Chunk& ch, int t0) {
-      if (pos >= 0 && t0 >= 0 && pos >= t0 && pos < t0 + kChunk) {
-        const int rr = pos - t0;
-        if ((rr & 3) == r) {
-          const U4 kn = ld16(a.k_new + grp * kHeadDim + col);
-          const U4 vn = ld16(a.v_new + grp * kHeadDim + col);
-          const int iv = rr >> 2;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (i == (iv ^ rperm)) ch.k[i] = kn;
-            if (i == iv) ch.v[i] = vn;
-          }
-        }
-      }
-    };
     auto row_of = [&](int cc) -> int { return cc < ce ? __builtin_amdgcn_readfirstlane(lds.row[cc - cb]) : 0; };
     Chunk ring[kDepth + 1];
     int tring[kDepth + 1];
@@ -598,7 +553,6 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
       tring[k] = tok(cc + k * NW);
       if (cc + k * NW < ce) {  // no loads past the pass
         load_chunk(ring[k], kp, vp, krow, row_of(cc + k * NW), loff);
-        patch(ring[k], tring[k]);
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -611,7 +565,6 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
           tring[k] = tok(cc + (kDepth + 1) * NW);
           if (cc + (kDepth + 1) * NW < ce) {
             load_chunk(ring[k], kp, vp, krow, row_of(cc + (kDepth + 1) * NW), loff);
-            patch(ring[k], tring[k]);
           }
           __builtin_amdgcn_sched_barrier(0);
           cc += NW;
@@ -636,40 +589,25 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
     ticket = __hip_atomic_fetch_add(a.counters + grp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   // Per-head state of this lane's row group: head h lives in lane 16 r + h
-  // (a DPP row broadcast). With RG = 2, row groups r and r + 2 (lanes l and
-  // l + 32) merge through one lane swap first. Every kept row-group state
-  // goes to LDS.
-  constexpr int RG = kRowGroups<NW>;
+  // (a DPP row broadcast). Every row-group state goes to LDS.
+  constexpr int RG = 4;
   constexpr int NE = NW * RG;
   float m_[G], l_[G];
   [&]<int... H>(std::integer_sequence<int, H...>) {
     ((m_[H] = dpp<kDppBcast0 + H>(st.m)), ...);
     ((l_[H] = dpp<kDppBcast0 + H>(st.l)), ...);
   }(std::make_integer_sequence<int, G>{});
-  if constexpr (RG == 2) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float mx = max_xor32(m_[h]);
-      const float w = (m_[h] == ninf) ? 0.f : fast_exp2(m_[h] - mx);
-      m_[h] = mx;
-      l_[h] = sum_xor32(l_[h] * w);
-#pragma unroll
-      for (int d = 0; d < 8; ++d) acc[h][d] = sum_xor32(acc[h][d] * w);
-    }
+  for (int h = 0; h < G; ++h) {
+    f4_t* dst = reinterpret_cast<f4_t*>(&lds.racc[wave][r][h][col]);
+    dst[0] = f4_t{acc[h][0], acc[h][1], acc[h][2], acc[h][3]};
+    dst[1] = f4_t{acc[h][4], acc[h][5], acc[h][6], acc[h][7]};
   }
-  if (r < RG) {
+  if (c == 0) {
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      f4_t* dst = reinterpret_cast<f4_t*>(&lds.racc[wave][r][h][col]);
-      dst[0] = f4_t{acc[h][0], acc[h][1], acc[h][2], acc[h][3]};
-      dst[1] = f4_t{acc[h][4], acc[h][5], acc[h][6], acc[h][7]};
-    }
-    if (c == 0) {
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        lds.rm[h][wave * RG + r] = m_[h];
-        lds.rl[h][wave * RG + r] = l_[h];
-      }
+      lds.rm[h][wave * RG + r] = m_[h];
+      lds.rl[h][wave * RG + r] = l_[h];
     }
   }
   lds_sync();
@@ -722,7 +660,7 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
         if (it % 64 == 0 && a.lse) a.lse[ob + it / 64] = lg[k] == ninf ? ninf : lg[k] * kLn2;
       }
     }
-    return true;
+    return;
   }
   if (tid == 0) lds.ticket = ticket;
   lds_sync();
@@ -736,7 +674,7 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
   // split holding the last ticket returns the ticket counter to zero and
   // advances the count once every ticket is taken.
   const uint32_t tk = lds.ticket;
-  const bool spread = !kCoherent && G >= 2 && S >= kSpreadSplits && S >= G;
+  const bool spread = G >= 2 && S >= kSpreadSplits && S >= G;
   const uint32_t first = spread ? (uint32_t)(S - G) : (uint32_t)(S - 1);
   const uint64_t tag = ((uint64_t)(epoch + 1u) << 32) | (uint32_t)S;
   if (spread || tk < first) {
@@ -757,7 +695,7 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) __hip_atomic_store(a.flags + grp * S + split, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tk < first) return false;
+    if (tk < first) return;
   }
 
   // Alg. 2, "Combine", in a merging split: its own partial stays in LDS;
@@ -779,20 +717,18 @@ __device__ __forceinline__ bool decode_split(const DecodeArgs& a, int bb, int hk
       __builtin_amdgcn_s_sleep(1);
   }
   __syncthreads();
-  if constexpr (!kCoherent && G >= 2) {
+  if constexpr (G >= 2) {
     if (spread)
       merge_head<G, 64 * NW>(a, grp, S, split, (int)(tk - first), ob, lds.own_o, lds.own_l, lds.w, lds.red);
     else
-      merge_tail<G, 64 * NW, kCoherent>(a, grp, S, split, ob, lds.own_o, lds.own_l, lds.w, lds.red);
+      merge_tail<G, 64 * NW>(a, grp, S, split, ob, lds.own_o, lds.own_l, lds.w, lds.red);
   } else {
-    merge_tail<G, 64 * NW, kCoherent>(a, grp, S, split, ob, lds.own_o, lds.own_l, lds.w, lds.red);
+    merge_tail<G, 64 * NW>(a, grp, S, split, ob, lds.own_o, lds.own_l, lds.w, lds.red);
   }
-  const bool last = tk == (uint32_t)(S - 1);
-  if (last && tid == 0) {
+  if (tk == (uint32_t)(S - 1) && tid == 0) {
     __hip_atomic_store(a.counters + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a.epochs + grp, epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  return last;
 }
 
 }  // namespace

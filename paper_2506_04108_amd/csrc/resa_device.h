@@ -33,23 +33,13 @@ __device__ __forceinline__ void lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// threadIdx.x through an opaque move. A persistent kernel runs several
-// phases in loops; values derived from the thread index (addresses, lane
-// roles) are then computed inside each phase instead of being hoisted to the
-// kernel entry and held in registers across every phase.
+// threadIdx.x through an opaque move: values derived from it (addresses, lane
+// roles) are computed where they are used instead of being hoisted to the
+// kernel entry and held in registers across the phases before.
 __device__ __forceinline__ int thread_id() {
   int t = threadIdx.x;
   __asm__ volatile("" : "+v"(t));
   return t;
-}
-
-// The thread index: opaque in the persistent step kernel (kOpaque, see
-// thread_id), plain otherwise (an opaque move would also keep the compiler
-// from reading uniform data with scalar loads).
-template <bool kOpaque>
-__device__ __forceinline__ int tid_of() {
-  if constexpr (kOpaque) return thread_id();
-  else return (int)threadIdx.x;
 }
 
 __device__ __forceinline__ U4 ld16(const void* p) {

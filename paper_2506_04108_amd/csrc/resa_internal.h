@@ -93,6 +93,7 @@ struct SelectArgs {
   uint32_t* counters;          // [B, Hkv], zero between calls
   int32_t blocks_per_wg;
   int32_t fused;               // top-n in the scoring kernel's last workgroup
+  int32_t lists;               // in-window lists from 8193 blocks on (decode step), not from 12289
   // Append fused in front of the selection (null k_new: plain selection).
   const uint16_t* k_new;       // [B, Hkv, D] key of the new token
   const uint16_t* v_new;       // [B, Hkv, D] value of the new token
@@ -124,19 +125,6 @@ struct DecodeArgs {
   uint32_t* counters;          // [B, Hkv] split tickets, zero between calls
   uint32_t* epochs;            // [B, Hkv] merged calls so far (kept from call to call)
   uint64_t* flags;             // [B, Hkv, S] split partial published: (epoch + 1) << 32 | S
-  const uint16_t* k_new;       // fused step: [B, Hkv, D] token appended in the same launch
-  const uint16_t* v_new;
-};
-
-// Fused decode step (append + selection + decode in one persistent launch).
-struct StepArgs {
-  SelectArgs s;
-  DecodeArgs d;
-  uint32_t* queue;             // [4]: score claims, decode claims, exits (zero between calls), error flag
-  uint32_t* ready;             // [B, Hkv]: selection of the group published (zero between calls)
-  int32_t nranges;             // score ranges per group (blocks_per_wg each)
-  int32_t score_items, dec_items;
-  uint32_t max_spins;          // bound of a decode split's wait for its group's selection
 };
 
 struct RectifyArgs {
@@ -166,7 +154,6 @@ hipError_t launch_append(const CacheArgs& c, const uint16_t* k_new, const uint16
                          int32_t* seq_lens, hipStream_t stream);
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
-hipError_t launch_step(const StepArgs& a, hipStream_t stream);
 hipError_t launch_rectify(const RectifyArgs& a, hipStream_t stream);
 hipError_t launch_clear(void* p, size_t bytes, hipStream_t stream);
 hipError_t launch_stream_read(const void* buf, size_t bytes, uint32_t* sink, uint32_t match,
@@ -177,9 +164,6 @@ int32_t select_fused_max_blocks();
 int32_t select_blocks_per_wg(int32_t batch, int32_t kv_heads, int32_t max_blocks_seq);
 int32_t select_hist_words(int32_t batch, int32_t kv_heads, int32_t max_blocks_seq);
 int32_t decode_auto_splits(int32_t batch, int32_t kv_heads, int32_t n_cap, int32_t block_size);
-int32_t step_blocks_per_range(int32_t batch, int32_t kv_heads, int32_t max_blocks_seq);
-int32_t step_hist_words(int32_t batch, int32_t kv_heads, int32_t max_blocks_seq);
-int32_t step_max_blocks();
 int32_t rectify_num_qblocks(int32_t group, int32_t f);
 int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked);
 // An upper bound on the key splits of any call with lengths up to

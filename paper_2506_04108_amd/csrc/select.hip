@@ -150,7 +150,7 @@ __global__ __launch_bounds__(NT) void k_select(SelectArgs a) {
   const int tid = threadIdx.x;
   const int hk = blockIdx.y, bb = blockIdx.z;
   const size_t grp = (size_t)bb * a.c.kv_heads + hk;
-  const RangeInfo ri = score_range<NT / 64, 1, false, window_lists(NJ, NT)>(a, bb, hk, blockIdx.x, gridDim.x, s_hist, s_score);
+  const RangeInfo ri = score_range<NT / 64, 1, window_lists(NJ, NT)>(a, bb, hk, blockIdx.x, gridDim.x, s_hist, s_score);
   if (!a.fused) return;
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(NT) void k_select(SelectArgs a) {
   __syncthreads();
   if (s_misc[3] != gridDim.x - 1) return;
   select_tail<NJ, NT>(a, grp, ri.M, ri.forced_from, gridDim.x, ri.win, s_hist, s_lds32, s_misc,
-                               reinterpret_cast<int32_t*>(s_score), bb, ri.sl.L, nullptr);
+                               reinterpret_cast<int32_t*>(s_score), bb, ri.sl.L);
 }
 
 }  // namespace
@@ -174,7 +174,11 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
     // the top-n of the last workgroup dominates, and half the waves share
     // the CU's SIMDs (4K batch 1 selection 9.9 -> 9.35 us, 32K batch 4
     // 14.2 -> 13.9 us; 64K batch 8, with 1024-block ranges, is slower so).
-    const int per = (a.max_blocks_seq + kSelThreads - 1) / kSelThreads;
+    // The decode step's workspace counts the calls that finish on the
+    // in-window path, from 8193 blocks on: there it takes 16 keys per thread,
+    // which have the path (8750 blocks, 16 groups: 22.5 us against 20.6).
+    int per = (a.max_blocks_seq + kSelThreads - 1) / kSelThreads;
+    if (a.lists && per > 8 && per < 16) per = 16;
     const int per_half = (a.max_blocks_seq + 511) / 512;
     const bool half = a.blocks_per_wg <= 256 && per_half <= 8;
     if (half && per_half <= 4)

@@ -1,5 +1,4 @@
-// Block selection (Sec. 2.1) device code shared by the selection kernels and
-// the fused decode step: average-pooled group query, Quest block score
+// Block selection (Sec. 2.1) device code: average-pooled group query, Quest block score
 // (Eq. 4) and the dynamic top-n (Eq. 5) with local forcing.
 #pragma once
 
@@ -34,8 +33,7 @@ __device__ __forceinline__ uint32_t block_key(int m, int forced_from, float s) {
 }
 
 // A buffer resource over a workgroup-uniform range (marked uniform for the
-// compiler: in the persistent step kernel the group index comes from LDS,
-// and a resource in vector registers would take a loop over the lanes).
+// compiler: a resource in vector registers would take a loop over the lanes).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(wave_uniform(p)), (short)0,
                                            (int)__builtin_amdgcn_readfirstlane(bytes), kBufWord3);
@@ -201,39 +199,28 @@ constexpr uint32_t kMaxCand = 256;  // bucket size resolved by ranking (NT / 256
 // instantiation that covers M, so the unrolled per-thread loops do no more
 // work than the group needs.
 //
-// The ids and the count go out with agent-scope stores. With `ready` set
-// (the fused decode step), the sequence length is left to the caller and,
-// once every store of the workgroup is acknowledged, ready[grp] is set for
-// the decode work of the group; otherwise the last group of a sequence
-// stores its new length (fused append).
+// The ids and the count go out with agent-scope stores. The last group of a
+// sequence stores its new length (fused append).
 template <int NJ, int NT>
 __device__ __forceinline__ void select_tail(const SelectArgs& a, size_t grp, int M, int forced_from, int W,
                                             uint32_t win, uint32_t* s_hist, uint32_t* lds32, uint32_t* misc,
-                                            int32_t* s_out, int bb, int L, uint32_t* ready) {
+                                            int32_t* s_out, int bb, int L) {
   static_assert(NJ <= 64 && NT % 256 == 0, "tail shape");
   using Mask = std::conditional_t<(NJ > 32), unsigned long long, uint32_t>;
   constexpr int kMaskBits = 8 * sizeof(Mask);
   const int tid = thread_id();
-  // Publishes the group's selection to the decode work of a fused step.
-  auto publish = [&]() {
-    if (ready == nullptr) return;
-    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) __hip_atomic_store(ready + grp, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
   const int n = count_selected(M, a.keep_ppm, a.min_blocks, a.n_local);
   int32_t* out = a.block_idx + grp * a.n_cap;
   if (n == 0 || n >= M) {
     if (tid == 0) {
       __hip_atomic_store(a.num_sel + grp, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(a.counters + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (a.k_new != nullptr && ready == nullptr)
+      if (a.k_new != nullptr)
         finish_append(a, bb, L, __hip_atomic_fetch_add(a.seq_counters + bb, 1u, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT));
     }
     for (int i = tid; i < a.n_cap; i += NT)
       __hip_atomic_store(out + i, i < n ? i : -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    publish();
     return;
   }
   const int id0 = tid * NJ;
@@ -279,7 +266,7 @@ __device__ __forceinline__ void select_tail(const SelectArgs& a, size_t grp, int
   // looked at after the selection, so the round trip overlaps the tail.
   uint32_t seq_ticket = 0;
   if (tid == 0) {
-    if (a.k_new != nullptr && ready == nullptr)
+    if (a.k_new != nullptr)
       seq_ticket = __hip_atomic_fetch_add(a.seq_counters + bb, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a.num_sel + grp, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(a.counters + grp, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -578,7 +565,7 @@ __device__ __forceinline__ void select_tail(const SelectArgs& a, size_t grp, int
   // The next call's window: the top 9 bits of this threshold. The stores
   // here go out before the compaction so their latency overlaps it.
   if (tid == 0) {
-    if (a.k_new != nullptr && ready == nullptr) finish_append(a, bb, L, seq_ticket);
+    if (a.k_new != nullptr) finish_append(a, bb, L, seq_ticket);
     a.window[grp] = 0x80000000u | (thr >> 23);
   }
 
@@ -621,7 +608,6 @@ __device__ __forceinline__ void select_tail(const SelectArgs& a, size_t grp, int
     for (int i = n + tid; i < a.n_cap; i += NT)
       __hip_atomic_store(out + i, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  publish();
 }
 
 // What the scoring workgroups of a group read of its sequence: the length
@@ -656,10 +642,10 @@ struct RangeInfo {
 // histogram slot, and with kLists writes the in-window path's above-window
 // bits and in-window list, all with agent-scope stores. Returns with those
 // stores issued (the caller waits for them before its ticket).
-template <int NW, int PF, bool kOpaque, bool kLists>
+template <int NW, int PF, bool kLists>
 __device__ __forceinline__ RangeInfo score_range(const SelectArgs& a, int bb, int hk, int range, int nranges,
                                                  uint32_t* s_hist, float* s_score) {
-  const int tid = tid_of<kOpaque>(), lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t grp = (size_t)bb * a.c.kv_heads + hk;
   const int r = lane >> 4, c = lane & 15, col = c * 8;
