@@ -34,12 +34,30 @@ def _ptr(t: torch.Tensor | None) -> int | None:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # The current stream of the current device, without building a Stream
+    # object for it (0.2 against 1.3 us).
+    return _raw_stream(_current_device())
+
+
+def _current_raw_stream(device: int) -> int:
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _current_raw_stream)
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
 def _need(t: torch.Tensor, name: str, dtype, shape=None):
+    # One expression for the usual case; which check failed is found out only
+    # where one did.
+    try:
+        if t.dtype is dtype and t.is_cuda and t.is_contiguous() and (shape is None or t.shape == shape) \
+                and isinstance(t, torch.Tensor):
+            return t
+    except AttributeError:
+        pass
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -112,22 +130,30 @@ class KVCache:
         return self.kmin.shape[2] * self.block_size
 
     def desc(self) -> KVCacheDesc:
-        for name in ("k", "v", "kmin", "kmax"):
-            _need(getattr(self, name), name, torch.bfloat16)
-        B, H, mb = self.kmin.shape[0], self.kmin.shape[1], self.kmin.shape[2]
-        if self.block_table is None:
-            _need(self.k, "k", torch.bfloat16, (B, H, mb * self.block_size, HEAD_DIM))
-            _need(self.v, "v", torch.bfloat16, (B, H, mb * self.block_size, HEAD_DIM))
-            return KVCacheDesc(self.k.data_ptr(), self.v.data_ptr(), self.kmin.data_ptr(),
-                               self.kmax.data_ptr(), B, H, HEAD_DIM, mb * self.block_size,
-                               self.block_size, None, 0)
-        P = self.k.shape[0]
-        _need(self.k, "k", torch.bfloat16, (P, H, self.block_size, HEAD_DIM))
-        _need(self.v, "v", torch.bfloat16, (P, H, self.block_size, HEAD_DIM))
-        _need(self.block_table, "block_table", torch.int32, (B, mb))
-        return KVCacheDesc(self.k.data_ptr(), self.v.data_ptr(), self.kmin.data_ptr(),
-                           self.kmax.data_ptr(), B, H, HEAD_DIM, mb * self.block_size,
-                           self.block_size, self.block_table.data_ptr(), P)
+        k, v, kmin, kmax, b, table = self.k, self.v, self.kmin, self.kmax, self.block_size, self.block_table
+        bf16 = torch.bfloat16
+        try:  # the usual case in one expression
+            fine = (k.dtype is bf16 and v.dtype is bf16 and kmin.dtype is bf16 and kmax.dtype is bf16 and k.is_cuda
+                    and v.is_cuda and kmin.is_cuda and kmax.is_cuda and k.is_contiguous() and v.is_contiguous()
+                    and kmin.is_contiguous() and kmax.is_contiguous())
+        except AttributeError:
+            fine = False
+        if not fine:
+            for name in ("k", "v", "kmin", "kmax"):
+                _need(getattr(self, name), name, bf16)
+        B, H, mb = kmin.shape[:3]
+        if table is None:
+            shape, pages, tp = (B, H, mb * b, HEAD_DIM), 0, None
+        else:
+            pages = k.shape[0]
+            shape = (pages, H, b, HEAD_DIM)
+        if k.shape != shape or v.shape != shape:
+            _need(k, "k", bf16, shape)
+            _need(v, "v", bf16, shape)
+        if table is not None:
+            tp = _need(table, "block_table", torch.int32, (B, mb)).data_ptr()
+        return KVCacheDesc(k.data_ptr(), v.data_ptr(), kmin.data_ptr(), kmax.data_ptr(), B, H, HEAD_DIM, mb * b,
+                           b, tp, pages)
 
 
 class Workspace:
@@ -193,7 +219,7 @@ def select_blocks(cache: KVCache, q: torch.Tensor, seq_lens: torch.Tensor, max_s
     Returns ``(block_idx [B, Hkv, n_cap] int32 ascending, -1 padded,
     num_sel [B, Hkv] int32)``.
     """
-    B, Hkv = cache.batch, cache.kv_heads
+    B, Hkv = cache.kmin.shape[0], cache.k.shape[1]
     hq = q.shape[1]
     _need(q, "q", torch.bfloat16, (B, hq, HEAD_DIM))
     _need(seq_lens, "seq_lens", torch.int32, (B,))
@@ -228,7 +254,7 @@ def append_select(cache: KVCache, k_new: torch.Tensor, v_new: torch.Tensor, q: t
     selection over the grown sequences (one launch); seq_lens is incremented
     in place. ``max_seq_len`` bounds seq_lens before the call. Returns
     ``(block_idx, num_sel)`` as :func:`select_blocks`."""
-    B, Hkv = cache.batch, cache.kv_heads
+    B, Hkv = cache.kmin.shape[0], cache.k.shape[1]
     hq = q.shape[1]
     shape = (B, Hkv, HEAD_DIM)
     _need(k_new, "k_new", torch.bfloat16, shape)
@@ -264,7 +290,7 @@ def sparse_decode(cache: KVCache, q: torch.Tensor, seq_lens: torch.Tensor, block
                   with_lse: bool = True, workspace: Workspace | None = None, stream=None):
     """Eq. 2 / Alg. 2 block-sparse flash decoding. Returns ``(out fp32 [B, Hq, 128],
     lse fp32 [B, Hq] or None)``."""
-    B, Hkv = cache.batch, cache.kv_heads
+    B, Hkv = cache.kmin.shape[0], cache.k.shape[1]
     hq = q.shape[1]
     _need(q, "q", torch.bfloat16, (B, hq, HEAD_DIM))
     _need(seq_lens, "seq_lens", torch.int32, (B,))
@@ -302,7 +328,7 @@ def decode_step(cache: KVCache, k_new: torch.Tensor, v_new: torch.Tensor, q: tor
     ``max_seq_len`` bounds seq_lens before the call. Returns
     ``(block_idx, num_sel, out, lse)`` as :func:`append_select` and
     :func:`sparse_decode`."""
-    B, Hkv = cache.batch, cache.kv_heads
+    B, Hkv = cache.kmin.shape[0], cache.k.shape[1]
     hq = q.shape[1]
     shape = (B, Hkv, HEAD_DIM)
     _need(k_new, "k_new", torch.bfloat16, shape)
@@ -348,7 +374,7 @@ def dense_rectify(cache: KVCache, q_f: torch.Tensor, k_f: torch.Tensor, v_f: tor
     """Sec. 2.2 rectification of the last f rows. Returns ``(out fp32 [B, Hq, f, 128], lse)``.
     ``seq_mask`` (int32 [B] on the device, or None for every sequence) selects the
     sequences rectified by this call; the others are left untouched."""
-    B, Hkv = cache.batch, cache.kv_heads
+    B, Hkv = cache.kmin.shape[0], cache.k.shape[1]
     hq, f = q_f.shape[1], q_f.shape[2]
     _need(q_f, "q_f", torch.bfloat16, (B, hq, f, HEAD_DIM))
     _need(k_f, "k_f", torch.bfloat16, (B, Hkv, f, HEAD_DIM))
