@@ -162,9 +162,137 @@ __global__ __launch_bounds__(NT) void k_select(SelectArgs a) {
                                reinterpret_cast<int32_t*>(s_score), bb, ri.sl.L);
 }
 
+// Selection of short groups (at most kSmallBlocks blocks): one workgroup scores
+// a whole group and selects in LDS, one block per thread, so that no key,
+// digit count or ticket crosses workgroups (three memory round trips of the
+// split kernel). The threshold's known bits come from the counts of the
+// scoring, as in select_tail; a bucket of more than kSmallCand keys is
+// narrowed by eight more bits at a time; the rest is ranked (key descending,
+// id ascending). Bound by latency: 256 blocks, 8 groups 8.5 -> 7.85 us, 64
+// groups 9.3 -> 8.4, 256 groups (250 blocks) 12.8 -> 10.2. The line: with more
+// blocks one CU reads too long for a group (313 blocks 8.65 -> 8.69 us, 438
+// 8.8 -> 10.6, 512 8.8 -> 11.5 at 8 groups; with 1024 threads 9.4 and 10.2).
+constexpr int kSmallBlocks = 320;
+constexpr int kSmallThreads = 512;
+constexpr uint32_t kSmallCand = 64;
+
+__global__ __launch_bounds__(kSmallThreads) void k_select_small(SelectArgs a) {
+  constexpr int NT = kSmallThreads;
+  __shared__ __attribute__((aligned(16))) uint32_t s_hist[2 * 256];
+  __shared__ __attribute__((aligned(16))) float s_score[kSmallBlocks];
+  __shared__ uint64_t s_cand[kSmallBlocks];
+  __shared__ uint32_t s_bits[kSmallBlocks / 32], s_wave[NT / 64], s_misc[8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hk = blockIdx.x, bb = blockIdx.y;
+  const size_t grp = (size_t)bb * a.c.kv_heads + hk;
+  if (tid < kSmallBlocks / 32) s_bits[tid] = 0;
+  if (tid == 0) s_misc[4] = 0;
+  const RangeInfo ri = score_range<NT / 64, 1, false, true>(a, bb, hk, 0, 1, s_hist, s_score);
+  // Every wave has read the old length (score_range's last barrier).
+  uint32_t seq_ticket = 0;
+  if (a.k_new != nullptr && tid == 0)
+    seq_ticket = __hip_atomic_fetch_add(a.seq_counters + bb, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int M = ri.M, n = count_selected(M, a.keep_ppm, a.min_blocks, a.n_local);
+  int32_t* out = a.block_idx + grp * a.n_cap;
+  bool keep = tid < M && n >= M;
+  if (n > 0 && n < M) {
+    const bool live = tid < M;
+    const uint32_t key = live ? block_key(tid, ri.forced_from, s_score[tid]) : 0u;
+    if (wave == 0) {
+      uint32_t top[4], wnd[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        top[j] = s_hist[4 * lane + j];
+        wnd[j] = s_hist[256 + 4 * lane + j];
+      }
+      const Threshold th = find_threshold(top, wnd, (uint32_t)n, ri.win, lane);
+      if (lane == 0) {
+        s_misc[0] = th.prefix;
+        s_misc[1] = th.k;
+        s_misc[2] = th.cnt;
+        s_misc[3] = th.known;
+      }
+    }
+    lds_sync();
+    uint32_t prefix = s_misc[0], k = s_misc[1], cnt = s_misc[2], known = s_misc[3];
+    uint32_t pmask = ~0u << (32 - known);
+    while (known < 32 && cnt != k && cnt > kSmallCand) {
+      const uint32_t width = min(8u, 32 - known), shift = 32 - known - width;
+      if (tid < 256) s_hist[tid] = 0;
+      lds_sync();
+      if (live && (key & pmask) == prefix) atomicAdd(&s_hist[(key >> shift) & ((1u << width) - 1u)], 1u);
+      lds_sync();
+      if (wave == 0) {
+        uint32_t c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[j] = s_hist[4 * lane + j];
+        const WaveDigit dg = wave_find_digit(c, k, lane);
+        if (lane == 0) {
+          s_misc[0] = prefix | (dg.d << shift);
+          s_misc[1] = dg.k;
+          s_misc[2] = dg.cnt;
+        }
+      }
+      lds_sync();
+      prefix = s_misc[0];
+      k = s_misc[1];
+      cnt = s_misc[2];
+      known += width;
+      pmask = ~0u << (32 - known);
+    }
+    const bool inb = live && (key & pmask) == prefix;
+    keep = live && (key & pmask) > prefix;
+    uint32_t thr = prefix;
+    if (cnt == k) {
+      keep = keep || inb;
+    } else {
+      const unsigned long long in = __ballot(inb);
+      uint32_t base = 0;
+      if (lane == 0 && in != 0) base = atomicAdd(&s_misc[4], (uint32_t)__builtin_popcountll(in));
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+      if (inb) s_cand[base + __builtin_popcountll(in & ((1ull << lane) - 1ull))] = ((uint64_t)key << 32) | (uint32_t)~(uint32_t)tid;
+      lds_sync();
+      if (tid < (int)cnt) {
+        const uint64_t v = s_cand[tid];
+        uint32_t before = 0;
+        for (uint32_t j = 0; j < cnt; ++j) before += s_cand[j] > v;
+        if (before < k) {
+          const uint32_t id = ~(uint32_t)v;
+          atomicOr(&s_bits[id >> 5], 1u << (id & 31u));
+          if (before == k - 1) s_misc[5] = (uint32_t)(v >> 32);  // the n-th largest key
+        }
+      }
+      lds_sync();
+      thr = s_misc[5];
+      if (live) keep = keep || ((s_bits[tid >> 5] >> (tid & 31)) & 1u) != 0;
+    }
+    // The next call's window: the top 9 bits of this threshold.
+    if (tid == 0) a.window[grp] = 0x80000000u | (thr >> 23);
+  }
+  // Kept ids in ascending order: thread order is id order.
+  const unsigned long long kept = __ballot(keep);
+  if (lane == 0) s_wave[wave] = (uint32_t)__builtin_popcountll(kept);
+  lds_sync();
+  uint32_t pos = (uint32_t)__builtin_popcountll(kept & ((1ull << lane) - 1ull));
+  for (int w = 0; w < wave; ++w) pos += s_wave[w];
+  if (keep && pos < (uint32_t)a.n_cap) out[pos] = tid;  // never past the row, whatever the scores
+  for (int i = n + tid; i < a.n_cap; i += NT) out[i] = -1;
+  if (tid == 0) {
+    a.num_sel[grp] = n;
+    if (a.k_new != nullptr) finish_append(a, bb, ri.sl.L, seq_ticket);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
+  if (a.max_blocks_seq > 0 && a.max_blocks_seq <= kSmallBlocks) {
+    SelectArgs s = a;
+    s.blocks_per_wg = (a.max_blocks_seq + 31) / 32 * 32;  // the whole group in one range
+    const dim3 grid(a.c.kv_heads, a.c.batch);
+    hipLaunchKernelGGL(k_select_small, grid, dim3(kSmallThreads), 0, stream, s);
+    return hipGetLastError();
+  }
   if (a.max_blocks_seq > 0) {
     dim3 grid((a.max_blocks_seq + a.blocks_per_wg - 1) / a.blocks_per_wg, a.c.kv_heads, a.c.batch);
     // Keys per thread of the fused top-n: the smallest instantiation that

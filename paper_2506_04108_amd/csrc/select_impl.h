@@ -158,6 +158,38 @@ __device__ __forceinline__ WaveDigit wave_find_digit(const uint32_t (&c)[4], uin
   return out;
 }
 
+// The known bits of the n-th largest key, by one wave: lane i holds the
+// counts of the keys' top bytes 4i .. 4i + 3 and, of the keys inside the
+// window hint, of their bits 22 .. 15. When the n-th largest key falls inside
+// the window, 17 bits are known at once; otherwise 8. k is its rank among the
+// cnt keys that share them.
+struct Threshold {
+  uint32_t prefix, k, cnt, known;
+};
+__device__ __forceinline__ Threshold find_threshold(const uint32_t (&top)[4], const uint32_t (&wnd)[4], uint32_t n,
+                                                    uint32_t win, int lane) {
+  if (win >> 31) {
+    const uint32_t w9 = win & 0x1FFu, w8 = w9 >> 1;
+    // Keys in the window, and keys above it (the other half of the window's
+    // top byte lies above it when W9 is even).
+    uint32_t y = 0, t8 = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      y += (uint32_t)(4 * lane + j) > w8 ? top[j] : 0u;
+      t8 = (uint32_t)j == (w8 & 3u) ? top[j] : t8;
+    }
+    const uint32_t inw = wave_sum(wnd[0] + wnd[1] + wnd[2] + wnd[3]);
+    uint32_t above = wave_sum(y);
+    if ((w9 & 1u) == 0) above += (uint32_t)__builtin_amdgcn_readlane((int)t8, (int)(w8 >> 2)) - inw;
+    if (above < n && n <= above + inw) {
+      const WaveDigit dg = wave_find_digit(wnd, n - above, lane);
+      return {(w9 << 23) | (dg.d << 15), dg.k, dg.cnt, 17u};
+    }
+  }
+  const WaveDigit dg = wave_find_digit(top, n, lane);
+  return {dg.d << 24, dg.k, dg.cnt, 8u};
+}
+
 // Keys [id0, id0 + NJ) of a group's key row (agent-scope loads; past the
 // row they read 0).
 template <int NJ>
@@ -307,39 +339,12 @@ __device__ __forceinline__ void select_tail(const SelectArgs& a, size_t grp, int
     const uint32_t q0 = packed[kSlotWords / 2 + 2 * lane], q1 = packed[kSlotWords / 2 + 2 * lane + 1];
     const uint32_t top[4] = {p0 & 0xFFFFu, p0 >> 16, p1 & 0xFFFFu, p1 >> 16};
     const uint32_t wnd[4] = {q0 & 0xFFFFu, q0 >> 16, q1 & 0xFFFFu, q1 >> 16};
-    const uint32_t kk = (uint32_t)n;
-    WaveDigit dg;
-    uint32_t pre = 0, kn = 8;
-    bool found = false;
-    if (win >> 31) {
-      const uint32_t w9 = win & 0x1FFu, w8 = w9 >> 1;
-      // Keys in the window, and keys above it (the other half of the
-      // window's top byte lies above it when W9 is even).
-      uint32_t y = 0, t8 = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        y += (uint32_t)(4 * lane + j) > w8 ? top[j] : 0u;
-        t8 = (uint32_t)j == (w8 & 3u) ? top[j] : t8;
-      }
-      const uint32_t inw = wave_sum(wnd[0] + wnd[1] + wnd[2] + wnd[3]);
-      uint32_t above = wave_sum(y);
-      if ((w9 & 1u) == 0) above += (uint32_t)__builtin_amdgcn_readlane((int)t8, (int)(w8 >> 2)) - inw;
-      if (above < kk && kk <= above + inw) {
-        dg = wave_find_digit(wnd, kk - above, lane);
-        pre = (w9 << 23) | (dg.d << 15);
-        kn = 17;
-        found = true;
-      }
-    }
-    if (!found) {
-      dg = wave_find_digit(top, kk, lane);
-      pre = dg.d << 24;
-    }
+    const Threshold th = find_threshold(top, wnd, (uint32_t)n, win, lane);
     if (lane == 0) {
-      misc[0] = pre;
-      misc[1] = dg.k;
-      misc[2] = dg.cnt;
-      misc[5] = kn;
+      misc[0] = th.prefix;
+      misc[1] = th.k;
+      misc[2] = th.cnt;
+      misc[5] = th.known;
     }
   }
   lds_sync();
@@ -641,8 +646,9 @@ struct RangeInfo {
 // keys' 8 high bits (and 8 more inside the window hint) into its own
 // histogram slot, and with kLists writes the in-window path's above-window
 // bits and in-window list, all with agent-scope stores. Returns with those
-// stores issued (the caller waits for them before its ticket).
-template <int NW, int PF, bool kLists>
+// stores issued (the caller waits for them before its ticket). With kLocal
+// the scores and the counts stay in LDS (scores go to scores_out if asked).
+template <int NW, int PF, bool kLists, bool kLocal = false>
 __device__ __forceinline__ RangeInfo score_range(const SelectArgs& a, int bb, int hk, int range, int nranges,
                                                  uint32_t* s_hist, float* s_score) {
   const int tid = threadIdx.x, lane = tid & 63;
@@ -805,7 +811,7 @@ __device__ __forceinline__ RangeInfo score_range(const SelectArgs& a, int bb, in
   const int nb = max(b1 - b0, 0);
   if (nb > 0) {
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(a.keys + grp * a.score_stride + b0, (uint32_t)nb * 4);
-    for (int i = 4 * tid; i < nb; i += 4 * NW * 64) {
+    for (int i = 4 * tid; !kLocal && i < nb; i += 4 * NW * 64) {
       const f4_t v = *reinterpret_cast<const f4_t*>(&s_score[i]);
       const int m = b0 + i;
       const U4 kv = U4{block_key(m, forced_from, v.x), block_key(m + 1, forced_from, v.y),
@@ -818,7 +824,7 @@ __device__ __forceinline__ RangeInfo score_range(const SelectArgs& a, int bb, in
       for (int i = tid; i < nb; i += NW * 64) so[i] = s_score[i];
     }
   }
-  if (!a.fused) return info;
+  if (kLocal || !a.fused) return info;
   if (kLists && win_on && nb > 0 && a.blocks_per_wg <= kListRange) {
     // For the top-n's in-window path: a bit per block whose key lies above
     // the window (one ballot per 64 blocks; the range starts on a word), and
