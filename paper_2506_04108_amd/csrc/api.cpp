@@ -166,19 +166,44 @@ DecodeLayout decode_layout(int32_t batch, int32_t kv_heads, int32_t group, int32
 }
 
 // Workspace of resa_decode_step: a status area (words 0 .. 63 and one word per
-// group, always zero), then a selection workspace and a decode workspace.
+// group, always zero), then what the selection and the decode keep from call
+// to call (tickets, window hints, counters; merge tickets and call counts) at
+// offsets that follow from the batch and the head count alone, then the
+// decode's flags and partials and the selection's scratch, whose sizes follow
+// the split count and the length: a workspace sized for the longest context
+// serves calls of any shorter one, in any order. (The decode's flags lie in
+// front of its partials and of the keys, as in its own workspace: a flag
+// matches only this call's tag, a small call count above the split count,
+// which neither partials nor keys look like.)
 struct StepLayout {
-  size_t sel, dec, total;
+  SelectLayout s;
   DecodeLayout d;
+  size_t total;
 };
 
 StepLayout step_layout(int32_t batch, int32_t kv_heads, int32_t group, int32_t sel_len,
                        int32_t block_size, int32_t splits) {
   StepLayout l;
-  l.sel = 256 + round256((size_t)batch * kv_heads * 4);
-  l.dec = l.sel + round256(select_layout(batch, kv_heads, sel_len, block_size).total);
-  l.d = decode_layout(batch, kv_heads, group, splits);
-  l.total = l.dec + l.d.total;
+  const size_t groups = (size_t)batch * kv_heads;
+  const SelectLayout s = select_layout(batch, kv_heads, sel_len, block_size);
+  const DecodeLayout d = decode_layout(batch, kv_heads, group, splits);
+  const size_t sel = 256 + round256(groups * 4);
+  l.s.counters = sel + s.counters;
+  l.s.seq_counters = sel + s.seq_counters;
+  l.s.window = sel + s.window;
+  l.s.stats = sel + s.stats;
+  const size_t dec = sel + s.hist;  // s.hist: the end of the selection's state
+  l.d.counters = dec + d.counters;
+  l.d.epochs = dec + d.epochs;
+  l.d.flags = dec + round256(d.flags);
+  l.d.lse = l.d.flags + round256(d.lse - d.flags);
+  l.d.o = l.d.lse + (d.o - d.lse);
+  l.d.total = l.d.o + round256(d.total - d.o);
+  l.s.keys = l.d.total;
+  l.s.above_bits = l.s.keys + (s.above_bits - s.keys);
+  l.s.win_keys = l.s.above_bits + (s.win_keys - s.above_bits);
+  l.s.hist = l.s.win_keys + round256(s.total - s.win_keys);
+  l.s.total = l.total = l.s.hist + (s.keys - s.hist);
   return l;
 }
 
@@ -268,7 +293,7 @@ int select_common(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
                   const int32_t* seq_lens, int32_t sel_len, const resa_select_params_t* params,
                   int32_t* block_idx, int32_t* num_sel, int32_t n_cap, float* scores_out,
                   void* workspace, size_t workspace_bytes, const void* k_new, const void* v_new,
-                  bool step, void* stream, const char* what) {
+                  const SelectLayout& lay, bool step, void* stream, const char* what) {
   int32_t group = 0;
   if (int e = check_heads(c, num_q_heads, &group)) return e;
   RESA_CHECK_PTR(q, 16);
@@ -288,7 +313,6 @@ int select_common(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
     return fail(RESA_ERR_CAPACITY, "n_cap %d < %d blocks selectable at %d tokens", n_cap, need,
                 sel_len);
   if (scores_out != nullptr) RESA_CHECK_PTR(scores_out, 4);
-  const SelectLayout lay = select_layout(c->batch, c->num_kv_heads, sel_len, c->block_size);
   if (workspace == nullptr || workspace_bytes < lay.total)
     return fail(RESA_ERR_WORKSPACE, "select workspace needs %zu bytes, got %zu", lay.total,
                 workspace == nullptr ? (size_t)0 : workspace_bytes);
@@ -341,7 +365,8 @@ int resa_select_blocks(const resa_kv_cache_t* c, const void* q, int32_t num_q_he
     return fail(RESA_ERR_INVALID_ARG, "max_seq_len %d outside [0, capacity %d]", max_seq_len,
                 c->capacity);
   return select_common(c, q, num_q_heads, seq_lens, max_seq_len, params, block_idx, num_sel, n_cap,
-                       scores_out, workspace, workspace_bytes, nullptr, nullptr, false, stream,
+                       scores_out, workspace, workspace_bytes, nullptr, nullptr,
+                       select_layout(c->batch, c->num_kv_heads, max_seq_len, c->block_size), false, stream,
                        "resa_select_blocks launch");
 }
 
@@ -358,7 +383,8 @@ int resa_append_select(const resa_kv_cache_t* c, const void* k_new, const void* 
     return fail(RESA_ERR_CAPACITY, "cache full: max_seq_len %d, capacity %d", max_seq_len,
                 c->capacity);
   return select_common(c, q, num_q_heads, seq_lens, max_seq_len + 1, params, block_idx, num_sel,
-                       n_cap, scores_out, workspace, workspace_bytes, k_new, v_new, false, stream,
+                       n_cap, scores_out, workspace, workspace_bytes, k_new, v_new,
+                       select_layout(c->batch, c->num_kv_heads, max_seq_len + 1, c->block_size), false, stream,
                        "resa_append_select launch");
 }
 
@@ -369,7 +395,7 @@ size_t resa_select_stats_offset(int32_t batch, int32_t num_kv_heads) {
 
 size_t resa_step_stats_offset(int32_t batch, int32_t num_kv_heads) {
   if (batch < 1 || num_kv_heads < 1) return 0;
-  return step_layout(batch, num_kv_heads, 1, 1, 16, 1).sel + select_layout_words(batch, num_kv_heads, 1, 1).stats;
+  return step_layout(batch, num_kv_heads, 1, 1, 16, 1).s.stats;
 }
 
 int32_t resa_decode_num_splits(int32_t batch, int32_t num_kv_heads, int32_t n_cap,
@@ -598,10 +624,10 @@ int resa_decode_step(const resa_kv_cache_t* c, const void* k_new, const void* v_
   char* ws = static_cast<char*>(workspace);
   // Every argument is checked: the two launches follow.
   if (int e = select_common(c, q, num_q_heads, seq_lens, sel_len, params, block_idx, num_sel, n_cap, nullptr,
-                            ws + lay.sel, lay.dec - lay.sel, k_new, v_new, true, stream, "resa_decode_step launch"))
+                            ws, workspace_bytes, k_new, v_new, lay.s, true, stream, "resa_decode_step launch"))
     return e;
   return decode_launch(c, q, num_q_heads, seq_lens, block_idx, num_sel, n_cap, group, splits, sm_scale, out, lse,
-                       ws + lay.dec, lay.d, false, stream, "resa_decode_step launch");
+                       ws, lay.d, false, stream, "resa_decode_step launch");
 }
 
 size_t resa_rectify_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t num_q_heads,
