@@ -307,9 +307,11 @@ size_t resa_step_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t num
  * Two kernels, the selection's and the decode's (one persistent kernel that
  * claimed both kinds of work measured 94 against 70 us at 64K batch 8 and 31
  * against 18 us at 4K). The workspace (resa_step_workspace_size) holds a
- * status area, a selection workspace and a decode workspace: zero-fill it
- * before its first use (resa_workspace_clear); every call leaves it ready for
- * the next. Calls sharing a workspace must be ordered on one stream.
+ * status area, what the selection and the decode keep from call to call (at
+ * offsets that follow from the batch and the head count) and their scratch:
+ * zero-fill it before its first use (resa_workspace_clear); every call leaves
+ * it ready for the next, of this or another length, n_cap or split count.
+ * Calls sharing a workspace must be ordered on one stream.
  * Status: the uint32 at byte offset 12 of the workspace is 0 after every call
  * (reserved for a launch that could not finish).
  */

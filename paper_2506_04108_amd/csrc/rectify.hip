@@ -800,7 +800,7 @@ int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max
   int64_t chunk = (max_seq_len + target - 1) / target;
   chunk = (chunk + kMaxKeyTile - 1) / kMaxKeyTile * kMaxKeyTile;
   if (chunk < kMinRectChunk) chunk = kMinRectChunk;
-  // At most kMaxRectSplits splits, so the combine's weights fit in LDS.
+  // At most kMaxRectSplits splits (the targets above stay below it).
   const int64_t least = ((int64_t)max_seq_len + kMaxRectSplits - 1) / kMaxRectSplits;
   if (chunk < least) chunk = (least + kMaxKeyTile - 1) / kMaxKeyTile * kMaxKeyTile;
   return (int32_t)chunk;
