@@ -686,6 +686,7 @@ int resa_dense_rectify(const resa_kv_cache_t* c, const void* q_f, const void* k_
   a.max_seq_len = max_seq_len;
   a.chunk = lay.chunk;
   a.num_splits = lay.splits;
+  a.ref_keys = resa::rectify_ref_keys(c->batch, c->num_kv_heads, group * f, max_seq_len);
   a.num_qblocks = lay.nq;
   a.scale_log2 = sm_scale * 1.4426950408889634f;
   a.out = out;

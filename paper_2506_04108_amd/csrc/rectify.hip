@@ -95,6 +95,13 @@ constexpr int kMaxRectSplits = 1024;              // splits per group (bounded b
 // needs its row maximum beforehand; the normalisation by the sum uses the
 // same reference.
 constexpr float kMaxWeightSum = 4096.f;
+// Every a.ref_keys keys the reference is taken again from the tile at hand,
+// also downwards (by at most this many bits, so that sums stay in range: a
+// split holds at most eight such ranges). The largest weight of that tile is
+// then exactly 1, and it is among the heaviest of its range: the error against
+// 64 bits falls with the number of references (32K, 7 heads a group: 2.07e-4
+// with one over all keys, 2.05e-4 with 16, 1.99e-4 with 32).
+constexpr float kRefDown = 8.f;
 
 // Tile rows are stored unpadded (256 B); 16-byte piece p of row r sits in
 // slot p ^ swz(r). swz is a bijection on r % 16, so the K operand reads (16
@@ -244,6 +251,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   constexpr int kRowsPerWg = kRowsPerWave * kWaves;
   constexpr int kTileBytes = kKT * kRowBytes;
   constexpr int kPolicy = kNt ? kPolicyNt : 0;
+  constexpr bool kRenew = kWaves == 8;           // 4 waves: one reference a split (see rectify_ref_keys)
   // Tile t sits in K and V stage t % 4. All of the workgroup's LDS is one
   // object: with several, the compiler tags each access with the object it
   // touches and makes reads wait for loads into the others.
@@ -610,13 +618,30 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
         }
         if (k0 + kKT > cut) mask(k0, sa);
         m = row_max(sa);
+        // The reference taken again, before the weights of tile `renew` are
+        // formed (between two rounds: within one it costs 6 % of a prefill).
+        int renew = (a.ref_keys - k0 % a.ref_keys) / kKT;
+        auto take_reference = [&](const f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
+          renew += a.ref_keys / kKT;
+          const float x = row_max(s);
+          const float mn = x == ninf ? m : fmaxf(x, m - kRefDown);
+          const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
+          m = mn;
+          l *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+        };
         for (int ti = 0; ti < ntiles; ti += 4) {
+          if (kRenew && __builtin_expect(ti == renew, 0)) take_reference(sa);
           round(ti, std::integral_constant<int, 0>{}, sa, sb);
           if (ti + 1 >= ntiles) break;
+          if (kRenew && __builtin_expect(ti + 1 == renew, 0)) take_reference(sb);
           round(ti + 1, std::integral_constant<int, 1>{}, sb, sa);
           if (ti + 2 >= ntiles) break;
+          if (kRenew && __builtin_expect(ti + 2 == renew, 0)) take_reference(sa);
           round(ti + 2, std::integral_constant<int, 2>{}, sa, sb);
           if (ti + 3 >= ntiles) break;
+          if (kRenew && __builtin_expect(ti + 3 == renew, 0)) take_reference(sb);
           round(ti + 3, std::integral_constant<int, 3>{}, sb, sa);
         }
         // No load may still be writing LDS when the stages are used again.
@@ -795,8 +820,7 @@ static int64_t rectify_target_splits(int32_t batch, int32_t kv_heads, int32_t ro
 // 30.4 against 34.0 us per call with a 512-key minimum).
 constexpr int kMinRectChunk = 128;
 
-int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked) {
-  const int64_t target = rectify_target_splits(batch, kv_heads, rows, masked);
+static int32_t chunk_for(int64_t target, int32_t max_seq_len) {
   int64_t chunk = (max_seq_len + target - 1) / target;
   chunk = (chunk + kMaxKeyTile - 1) / kMaxKeyTile * kMaxKeyTile;
   if (chunk < kMinRectChunk) chunk = kMinRectChunk;
@@ -804,6 +828,19 @@ int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max
   const int64_t least = ((int64_t)max_seq_len + kMaxRectSplits - 1) / kMaxRectSplits;
   if (chunk < least) chunk = (least + kMaxKeyTile - 1) / kMaxKeyTile * kMaxKeyTile;
   return (int32_t)chunk;
+}
+
+int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked) {
+  return chunk_for(rectify_target_splits(batch, kv_heads, rows, masked), max_seq_len);
+}
+
+// Keys a softmax reference serves, at most: those of a split when the query
+// blocks are dealt to about 512 workgroups (which windows of up to 128 rows
+// are, so one reference a split there).
+int32_t rectify_ref_keys(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len) {
+  const int32_t per = waves_for_rows(rows) * kRowsPerWave;
+  const int64_t wgs = (int64_t)batch * kv_heads * ((rows + per - 1) / per);
+  return chunk_for((512 + wgs - 1) / wgs, max_seq_len);
 }
 
 int32_t rectify_max_splits(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len) {

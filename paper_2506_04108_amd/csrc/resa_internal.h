@@ -137,6 +137,7 @@ struct RectifyArgs {
   int32_t max_seq_len;
   int32_t chunk;               // keys per split
   int32_t num_splits;          // ceil(max_seq_len / chunk)
+  int32_t ref_keys;            // keys a softmax reference serves, a multiple of 64
   int32_t num_qblocks;         // query blocks per group
   float scale_log2;
   float* out;                  // [B, Hq, f, D]
@@ -166,6 +167,7 @@ int32_t select_hist_words(int32_t batch, int32_t kv_heads, int32_t max_blocks_se
 int32_t decode_auto_splits(int32_t batch, int32_t kv_heads, int32_t n_cap, int32_t block_size);
 int32_t rectify_num_qblocks(int32_t group, int32_t f);
 int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked);
+int32_t rectify_ref_keys(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len);
 // An upper bound on the key splits of any call with lengths up to
 // max_seq_len, non-decreasing in max_seq_len (workspace sizing).
 int32_t rectify_max_splits(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len);

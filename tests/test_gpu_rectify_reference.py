@@ -1,0 +1,55 @@
+"""The softmax reference of the rectification: where it is taken, that it is
+found again after a tile without a finite score, and softmax scales of every
+sign. Against the oracle, with logits that are set key by key."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2506_04108_amd as R
+import workloads as W
+from gpu_util import i32, make_cache, up
+from oracle.compare import max_abs_err
+
+pytestmark = pytest.mark.gpu
+
+
+def rectify(K, V, q, f, sm_scale):
+    """The last f rows of K and V, written again, and the oracle's result for
+    query rows q [B, Hq, f, 128]; all bf16 bits."""
+    L = K.shape[2]
+    cache = make_cache(K, V, 16, sentinel=False)
+    lt = i32([L] * K.shape[0])
+    R.block_summarize(cache, lt)
+    kf, vf = np.ascontiguousarray(K[:, :, L - f:]), np.ascontiguousarray(V[:, :, L - f:])
+    out, lse = R.dense_rectify(cache, up(q), up(kf), up(vf), lt, L, sm_scale=sm_scale)
+    torch.cuda.synchronize()
+    st = O.DecodeState(O.bf16_to_f64(K), O.bf16_to_f64(V), [L] * K.shape[0], 16)
+    ro, rl = st.rectify(O.bf16_to_f64(q), O.bf16_to_f64(kf), O.bf16_to_f64(vf), f, sm_scale)
+    return out.cpu().numpy(), lse.cpu().numpy(), ro, rl
+
+
+def test_reference_taken_again_within_a_split():
+    """32 groups of 129 rows over 2048 keys: 8 splits of 256 keys, the
+    reference taken every 128. One key a group, at the second range of a
+    split, carries nearly all of the weight, 1024.4 times that of the range
+    before it: against that range's reference it is rounded to 1024 (3.9e-4
+    off), against its own it is exactly 1. Bound: fp32 rounding (2e-6)."""
+    B, H, f, L = 8, 4, 129, 2048
+    K = np.zeros((B, H, L, 128), np.float32)
+    V = np.zeros((B, H, L, 128), np.float32)
+    q = np.zeros((B, H, f, 128), np.float32)
+    q[..., :2] = 1.0
+    K[..., 0] = -10.0
+    y = np.log(1024.4)
+    y0 = float(W.bf16_bits_to_f32(W.f32_to_bf16_bits(np.array([y], np.float32)))[0])
+    for bi in range(B):
+        for hi in range(H):
+            at = 256 * ((4 * bi + hi) % 7)
+            K[bi, hi, at + 3, 0] = 0.0
+            K[bi, hi, at + 128 + 7 * hi, :2] = y0, y - y0
+            V[bi, hi, at + 128 + 7 * hi] = 1.0
+    go, gl, ro, rl = rectify(*(W.f32_to_bf16_bits(x) for x in (K, V, q)), f, 1.0)
+    eo, el = max_abs_err(go, ro), max_abs_err(gl, rl)
+    print(f"reference within a split: |dO| {eo:.2e} |dlse| {el:.2e}", flush=True)
+    assert eo <= 2e-6 and el <= 1e-5
