@@ -479,7 +479,6 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
       // operand reads and four weights; the scheduling barriers keep the
       // order. Returns the sum of the weights over this lane's keys.
       auto weights_scores = [&](auto stage, const f32x16_t (&s)[kKT32], f32x16_t (&sn)[kKT32], f16x8_t (&ph)[2 * kKT32]) __attribute__((always_inline)) {
-        const float mref = m == ninf ? 0.f : m;
         float ps[4] = {0.f, 0.f, 0.f, 0.f};
         bf16x8_t ka[2][kKT32];
         read_k(stage, 0, ka[0]);
@@ -497,7 +496,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
           for (int kt = 0; kt < kKT32; ++kt) sn[kt] = mfma32(ka[ks & 1][kt], qb[ks], sn[kt]);
 #pragma unroll
-          for (int i = 2 * kKT32 * ks; i < 2 * kKT32 * (ks + 1); ++i) weight(s, i, mref, ph, ps);
+          for (int i = 2 * kKT32 * ks; i < 2 * kKT32 * (ks + 1); ++i) weight(s, i, m, ph, ps);
           __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
@@ -528,9 +527,12 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
         f16x8_t ph[2 * kKT32];
         __builtin_amdgcn_sched_barrier(0);
         float ps = weights_scores(std::integral_constant<int, (st + 1) & 3>{}, s, sn, ph);
-        if (__builtin_expect(__any(ps > kMaxWeightSum), 0)) {  // rare: move the reference, form the weights again
+        // Rare: move the reference and form the weights again. A row without
+        // one so far (no tile with a finite score) has weights of inf or NaN
+        // and takes this branch too, on every tile until one has.
+        if (__builtin_expect(__any(!(ps <= kMaxWeightSum)), 0)) {
           const float mn = fmaxf(m, row_max(s));
-          const float alpha = fast_exp2(m - mn);
+          const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
           m = mn;
           l *= alpha;
 #pragma unroll

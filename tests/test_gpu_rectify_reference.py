@@ -53,3 +53,23 @@ def test_reference_taken_again_within_a_split():
     eo, el = max_abs_err(go, ro), max_abs_err(gl, rl)
     print(f"reference within a split: |dO| {eo:.2e} |dlse| {el:.2e}", flush=True)
     assert eo <= 2e-6 and el <= 1e-5
+
+
+@pytest.mark.parametrize("g,f", [(1, 8), (4, 32), (8, 17), (2, 200)])
+def test_first_tile_without_a_finite_score(g, f):
+    """Every second 64-key stretch scores -inf (the products overflow), so
+    most splits begin with a tile that has no finite score; the other keys'
+    logits are -40 (57 bits below zero). Bound: weights rounded to fp16
+    (2^-12) times the largest |V| (below 4.9)."""
+    B, H, L = 2, 2, 1500
+    w = W.TINY_4K.with_(batch=B, num_kv_heads=H, num_q_heads=H * g, seq_len=L, seed_tag=f"inf{g}-{f}")
+    V = W.kv_cache(w, capacity=1536)[1][:, :, :L + 4]
+    K = np.zeros((B, H, L + 4, 128), np.float32)
+    K[..., 1] = -40.0
+    K[..., 0] = np.where(np.arange(L + 4) % 128 < 64, -3e38, 0.0)
+    q = np.zeros((B, H * g, f, 128), np.float32)
+    q[..., 0], q[..., 1] = 1e30, 1.0
+    go, gl, ro, rl = rectify(W.f32_to_bf16_bits(K), V, W.f32_to_bf16_bits(q), f, 1.0)
+    eo, el = max_abs_err(go, ro), max_abs_err(gl, rl)
+    print(f"first tile -inf g={g} f={f}: |dO| {eo:.2e} |dlse| {el:.2e}", flush=True)
+    assert eo <= 1.2e-3 and el <= 1e-4
