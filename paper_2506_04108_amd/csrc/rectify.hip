@@ -713,10 +713,13 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 // 512-byte load of the wave; a wave takes 64 splits at a time, whose lse sit
 // one per lane: their weights are formed by all lanes at once and broadcast
 // one by one, with the partial loads of 16 splits in flight. One wave per row
-// where the splits are few (up to 16) and rows many; four otherwise.
+// where the splits are few (up to 16) and rows many; four otherwise. The
+// weights carry a factor of 1 / (2 kMaxRectSplits), which the normalisation
+// takes out again, so sums of rows near the largest float stay in range.
 template <int kPerRow>
 __global__ __launch_bounds__(256) void k_rectify_combine(RectifyArgs a) {
   constexpr int kRows = 4 / kPerRow;   // query rows per workgroup
+  constexpr float kScale = 0.5f / kMaxRectSplits;
   __shared__ f2_t s_acc[4][64];
   __shared__ float s_m[4], s_l[4];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -736,7 +739,7 @@ __global__ __launch_bounds__(256) void k_rectify_combine(RectifyArgs a) {
     const int cnt = min(64, n - b);
     const float x = lane < cnt ? pl[(size_t)((b + lane) * kPerRow + part) * R] : ninf;
     const float mn = fmaxf(m, wave_max_f(x));
-    const float e = x == ninf ? 0.f : fast_exp2(x - mn);
+    const float e = x == ninf ? 0.f : fast_exp2(x - mn) * kScale;
     const float alpha = m == ninf ? 0.f : fast_exp2(m - mn);
     l = fmaf(l, alpha, wave_sum_f(e));
     acc *= alpha;
@@ -778,7 +781,7 @@ __global__ __launch_bounds__(256) void k_rectify_combine(RectifyArgs a) {
   if (!live) return;
   const size_t oi = ((size_t)bb * a.q_heads + (size_t)hk * G + rho % G) * f + rho / G;
   *reinterpret_cast<f2_t*>(a.out + oi * kHeadDim + 2 * lane) = acc * (l > 0.f ? 1.f / l : 0.f);
-  if (lane == 0 && a.lse) a.lse[oi] = l > 0.f ? (m + fast_log2(l)) * kLn2 : ninf;
+  if (lane == 0 && a.lse) a.lse[oi] = l > 0.f ? (m + fast_log2(l * (1.f / kScale))) * kLn2 : ninf;
 }
 
 }  // namespace
