@@ -357,9 +357,8 @@ size_t resa_rectify_workspace_size(int32_t batch, int32_t num_kv_heads,
  * matrix cores with P in [0, 2^12]; V enters at its own scale (exact for
  * |v| in 2^-14 .. 65280, fp16 subnormal spacing 2^-24 below). Where a range of
  * keys holds larger values, the workgroups that read it repeat their pass
- * with each head dimension scaled by a power of two (the dimension's smaller
- * values then lose the bits below 2^-24 of the scale, far below 2e-3 of its
- * largest magnitude).
+ * with V split by magnitude into parts that are exact in fp16 at a power of
+ * two each, so a row's error follows the values that the row attends to.
  * Errors: RESA_ERR_INVALID_ARG for the ranges above or misaligned pointers,
  * RESA_ERR_WORKSPACE when a needed workspace is missing or too small.
  * The same call serves (chunked) prefill (Alg. 1, prefill step): with

@@ -42,16 +42,16 @@
 // half-round phases (8050 against 7910 us), V staged raw in LDS three tiles
 // ahead (8850 against 8540), one barrier per tile (7930 against 7770).
 //
-// V is used in fp16, each head dimension d multiplied by a power of two
-// 2^-E_d, E_d = 0 unless a value needs it. Every bf16 value of magnitude
-// 2^-14 .. 65280 is an fp16 value (8 significant bits fit in 11), so in that
-// range the conversion is exact; smaller values keep fp16's subnormal spacing
-// of 2^-24 (an error of at most 2^-24 * P per key). A value above 65504 is
-// noticed when it is converted; the workgroup then finishes the pass, takes
-// the largest |V| of each dimension over its keys and repeats the pass with
-// E_d such that max |v| 2^-E_d < 2^16 (such values do not occur in a model's
-// caches; the second pass keeps every finite bf16 V finite). Rows are
-// multiplied back by 2^E_d after the normalisation by the softmax sum.
+// V is used in fp16. Every bf16 value of magnitude 2^-14 .. 65280 is an fp16
+// value (8 significant bits fit in 11), so in that range the conversion is
+// exact; smaller values keep fp16's subnormal spacing of 2^-24 (an error of at
+// most 2^-24 * P per key). A value above 65504 is noticed when it is
+// converted; the workgroup then finishes the pass and takes its range again
+// with V split by magnitude (see kBandExp), each part exact in fp16, so that
+// every finite bf16 V gives a finite result and no row loses precision to a
+// value it does not see. Such values do not occur in a model's caches: the
+// second pass is a plain loop (64K rectification, batch 8: 1143 us with one
+// large value in every group, 400 with none).
 // Masking (causal cut, end of the split) is only evaluated on the tiles that
 // reach it. A second kernel merges the splits by log-sum-exp (Alg. 2,
 // "Combine"), spread over many workgroups.
@@ -102,6 +102,19 @@ constexpr float kMaxWeightSum = 4096.f;
 // 64 bits falls with the number of references (32K, 7 heads a group: 2.07e-4
 // with one over all keys, 2.05e-4 with 16, 1.99e-4 with 32).
 constexpr float kRefDown = 8.f;
+
+// V values above the fp16 range: band b > 0 holds magnitudes from
+// 2^(16 + 30 (b - 1)) up to 2^(16 + 30 b) (b = 4: and infinities and NaN),
+// which times 2^-30b are fp16 values of the normal range (2^-14 .. 2^16, the 8
+// significant bits of a bf16 value fit); band 0 all below 2^16. The
+// accumulators then carry 2^-40, so that sums of weights up to 2^32 times the
+// largest float stay in range (what is lost lies below 2^-109 of a weight).
+constexpr int kBandExp = 30, kLargeExp = -40;
+__device__ __forceinline__ int band_of(uint32_t w) {  // of the bf16 value in the upper half of w
+  const int e = (int)((w >> 23) & 0xff);
+  return e < 143 ? 0 : min((e - 143) / kBandExp + 1, 4);
+}
+__device__ __forceinline__ constexpr float exp2_of(int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); }
 
 // Tile rows are stored unpadded (256 B); 16-byte piece p of row r sits in
 // slot p ^ swz(r). swz is a bijection on r % 16, so the K operand reads (16
@@ -259,8 +272,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     uint8_t k[4][kTileBytes];
     uint8_t v[4][kTileBytes];   // fp16
     int large;                  // a V value above the fp16 range was met
-    float vscale[kHeadDim];     // 2^-E_d (second pass)
-    uint32_t vmax[kHeadDim];    // max |v| (fp32 bits: non-negative values order as integers)
+    uint32_t bands[2];          // bands of V in the tile at hand (tiles in turn)
   };
   __shared__ __attribute__((aligned(1024))) Lds lds;
   // The wave index is uniform per wave (readfirstlane tells the compiler), so
@@ -336,17 +348,17 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     for (int kt = 0; kt < kKT32; ++kt)
       ka[kt] = *(lds_bf16x8*)(uintptr_t)(kaddr[ks] + st * kTileBytes + kt * 32 * kRowBytes);
   };
+  auto read_v32 = [&](int st, int ks, int dt) __attribute__((always_inline)) -> f16x8_t {
+    f16x4_t x[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      x[e] = __builtin_bit_cast(f16x4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                 (lds_i16x4*)(uintptr_t)(vaddr[dt][e] + st * kTileBytes + 16 * ks * kRowBytes)));
+    return __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7);
+  };
   auto read_v = [&](auto stage, int ks, f16x8_t (&va)[4]) __attribute__((always_inline)) {
-    constexpr int st = decltype(stage)::value;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      f16x4_t x[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-        x[e] = __builtin_bit_cast(f16x4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                   (lds_i16x4*)(uintptr_t)(vaddr[dt][e] + st * kTileBytes + 16 * ks * kRowBytes)));
-      va[dt] = __builtin_shufflevector(x[0], x[1], 0, 1, 2, 3, 4, 5, 6, 7);
-    }
+    for (int dt = 0; dt < 4; ++dt) va[dt] = read_v32(decltype(stage)::value, ks, dt);
   };
 
   for (int half = 0; half < 2; ++half) {
@@ -422,17 +434,13 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
       vv[0] = __builtin_bit_cast(U4, __builtin_amdgcn_raw_buffer_load_b128(rv, off0, 0, kPolicy));
       vv[1] = __builtin_bit_cast(U4, __builtin_amdgcn_raw_buffer_load_b128(rv, off1, 0, kPolicy));
     };
-    // Piece e of vv to V stage st in fp16 (times the dimensions' factors).
-    auto put_v = [&](int st, int e, bool use_sc, float& vmax) __attribute__((always_inline)) {
+    // Piece e of vv to V stage st in fp16; vmax collects the largest magnitude.
+    auto put_v = [&](int st, int e, float& vmax) __attribute__((always_inline)) {
       const uint32_t w[4] = {vv[e].x, vv[e].y, vv[e].z, vv[e].w};
       uint32_t h[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        float x0 = bf_lo(w[i]), x1 = bf_hi(w[i]);
-        if (use_sc) {
-          x0 *= lds.vscale[8 * piece_of(e) + 2 * i];
-          x1 *= lds.vscale[8 * piece_of(e) + 2 * i + 1];
-        }
+        const float x0 = bf_lo(w[i]), x1 = bf_hi(w[i]);
         vmax = fmaxf(vmax, fmaxf(fabsf(x0), fabsf(x1)));
         h[i] = __builtin_bit_cast(uint32_t, f16x2_t{(_Float16)x0, (_Float16)x1});
       }
@@ -440,246 +448,299 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     };
 
     f32x16_t o[4];
-    float m, l;
-    bool scaled = false;
-    // A second pass only if the first met a V value above the fp16 range.
-    for (;;) {
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
+    float m = ninf, l = 0.f;  // l: over this lane's keys; summed across the two halves at the end
+    if (tid == 0) {
+      lds.large = 0;
+      lds.bands[0] = lds.bands[1] = 0u;
+    }
+    lds_sync();
+
+    auto mask = [&](int t0, f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
+      const int d = lim - t0 - 4 * hi;
+#pragma unroll
+      for (int kt = 0; kt < kKT32; ++kt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[kt][i] = 32 * kt + 8 * (i >> 2) + (i & 3) > d ? ninf : s[kt][i];
+    };
+    auto row_max = [&](const f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
+      float x = ninf;
+#pragma unroll
+      for (int kt = 0; kt < kKT32; ++kt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x = fmaxf(x, s[kt][i] * c);
+      return max_xor32(x);
+    };
+    // Weight i of the tile: raw score times c is its log2-domain logit.
+    auto weight = [&](const f32x16_t (&s)[kKT32], int i, float mref, f16x8_t (&ph)[2 * kKT32], float (&ps)[4]) __attribute__((always_inline)) {
+      const float pe = fast_exp2(fmaf(s[i >> 4][i & 15], c, -mref));
+      ps[i & 3] += pe;
+      ph[i >> 3][i & 7] = (_Float16)pe;
+    };
+    // Weights of one tile (scores s) interleaved with the scores of the
+    // next (K stage `stage`, into sn): per step two MFMAs, the next step's
+    // operand reads and four weights; the scheduling barriers keep the
+    // order. Returns the sum of the weights over this lane's keys.
+    auto weights_scores = [&](auto stage, const f32x16_t (&s)[kKT32], f32x16_t (&sn)[kKT32], f16x8_t (&ph)[2 * kKT32]) __attribute__((always_inline)) {
+      float ps[4] = {0.f, 0.f, 0.f, 0.f};
+      bf16x8_t ka[2][kKT32];
+      read_k(stage, 0, ka[0]);
+#pragma unroll
+      for (int kt = 0; kt < kKT32; ++kt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sn[kt][i] = 0.f;
+      __builtin_amdgcn_sched_barrier(0);
+      // The SIMD's other wave, at another point of its round, fills the gaps
+      // instead of delaying the MFMAs (8K prompts 4361 -> 4284 us).
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        if (ks < 7) read_k(stage, ks + 1, ka[(ks + 1) & 1]);
+#pragma unroll
+        for (int kt = 0; kt < kKT32; ++kt) sn[kt] = mfma32(ka[ks & 1][kt], qb[ks], sn[kt]);
+#pragma unroll
+        for (int i = 2 * kKT32 * ks; i < 2 * kKT32 * (ks + 1); ++i) weight(s, i, m, ph, ps);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_setprio(0);
+      return (ps[0] + ps[1]) + (ps[2] + ps[3]);
+    };
+    // One tile: its weights (scores s) with the next tile's scores (sn),
+    // then its P.V, with the conversion of the V of the tile after next.
+    //
+    // Order between the waves, with a barrier before every even tile 2p
+    // only. Rounds 2p and 2p + 1 read K(2p + 1), K(2p + 2), V(2p) and
+    // V(2p + 1); they write V(2p + 2) and V(2p + 3), into the stages last
+    // read in rounds 2p - 2 and 2p - 1, and at the end of round 2p request
+    // K(2p + 3) and K(2p + 4), into the stages last read in the same two
+    // rounds. All these were before the barrier, and what is written is
+    // read after the next one, at which every wave has waited for its own
+    // loads and stores: vmcnt counts in order, and only the two loads of
+    // V(2p + 2), issued after the K loads that are needed, may be pending.
+    // Tiles past the end are requested and converted too (empty
+    // resources: zeros), so the counts never change.
+    auto round = [&](int ti, auto stage, f32x16_t (&s)[kKT32], f32x16_t (&sn)[kKT32]) __attribute__((always_inline)) {
+      constexpr int st = decltype(stage)::value;
+      const int t0 = k0 + ti * kKT;
+      if constexpr (st % 2 == 0) {
+        __builtin_amdgcn_s_waitcnt(wait_vm(kPaged ? 3 : 2));
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        bare_barrier();
+      }
+      f16x8_t ph[2 * kKT32];
+      __builtin_amdgcn_sched_barrier(0);
+      float ps = weights_scores(std::integral_constant<int, (st + 1) & 3>{}, s, sn, ph);
+      // Rare: move the reference and form the weights again. A row without
+      // one so far (no tile with a finite score) has weights of inf or NaN
+      // and takes this branch too, on every tile until one has.
+      if (__builtin_expect(__any(!(ps <= kMaxWeightSum)), 0)) {
+        const float mn = fmaxf(m, row_max(s));
+        const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+        const float mref = m == ninf ? 0.f : m;
+        float pt[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16 * kKT32; ++i) weight(s, i, mref, ph, pt);
+        ps = (pt[0] + pt[1]) + (pt[2] + pt[3]);
+      }
+      l += ps;
+      if (__builtin_expect(t0 + 2 * kKT > cut, 0)) mask(t0 + kKT, sn);
+      __builtin_amdgcn_sched_barrier(0);
+      f16x8_t va[2][4];
+      read_v(stage, 0, va[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int nv = (st + 2) & 3;
+      float vmax = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 2 * kKT32; ++ks) {
+        if (ks < 2 * kKT32 - 1) read_v(stage, ks + 1, va[(ks + 1) & 1]);
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) o[dt] = mfma32(va[ks & 1][dt], ph[ks], o[dt]);
+        if (ks >= 2 * kKT32 - 2) put_v(nv, ks - (2 * kKT32 - 2), vmax);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (__builtin_expect(__any(!(vmax <= 65504.f)), 0)) lds.large = 1;
+      // Here the pages of tiles ti + 3 and ti + 4 have arrived (with the V
+      // pieces converted above, or earlier).
+      const int g3 = page_of(p3), g4 = page_of(p4);
+      if constexpr (st % 2 == 0) {
+        issue_k(ti + 3, (st + 3) & 3, g3);
+        issue_k(ti + 4, st, g4);
+      }
+      p3 = p4;
+      p4 = ask_page(ti + 5);
+      load_v(ti + 3, g3);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+
+    if (ntiles > 0) {
+      f32x16_t sa[kKT32], sb[kKT32];
+      // Pipeline start: everything is requested before anything is used.
+      const int asked[3] = {ask_page(0), ask_page(1), ask_page(2)};
+      p3 = ask_page(3);
+      p4 = ask_page(4);
+      const int pg[3] = {page_of(asked[0]), page_of(asked[1]), page_of(asked[2])};
+      load_v(0, pg[0]);
+      const U4 v0[2] = {vv[0], vv[1]};
+      load_v(1, pg[1]);
+      const U4 v1[2] = {vv[0], vv[1]};
+#pragma unroll
+      for (int t = 0; t < 3; ++t) issue_k(t, t, pg[t]);
+      float vmax = 0.f;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) vv[e] = v0[e];
+      put_v(0, 0, vmax);
+      put_v(0, 1, vmax);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) vv[e] = v1[e];
+      put_v(1, 0, vmax);
+      put_v(1, 1, vmax);
+      if (!(vmax <= 65504.f)) lds.large = 1;
+      load_v(2, pg[2]);
+      __builtin_amdgcn_s_waitcnt(wait_vm(2));
+      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      bare_barrier();
+      {
+        bf16x8_t ka[kKT32];
+#pragma unroll
+        for (int kt = 0; kt < kKT32; ++kt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sa[kt][i] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          read_k(std::integral_constant<int, 0>{}, ks, ka);
+#pragma unroll
+          for (int kt = 0; kt < kKT32; ++kt) sa[kt] = mfma32(ka[kt], qb[ks], sa[kt]);
+        }
+      }
+      if (k0 + kKT > cut) mask(k0, sa);
+      m = row_max(sa);
+      // The reference taken again, before the weights of tile `renew` are
+      // formed (between two rounds: within one it costs 6 % of a prefill).
+      int renew = (a.ref_keys - k0 % a.ref_keys) / kKT;
+      auto take_reference = [&](const f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
+        renew += a.ref_keys / kKT;
+        const float x = row_max(s);
+        const float mn = x == ninf ? m : fmaxf(x, m - kRefDown);
+        const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+      };
+      for (int ti = 0; ti < ntiles; ti += 4) {
+        if (kRenew && __builtin_expect(ti == renew, 0)) take_reference(sa);
+        round(ti, std::integral_constant<int, 0>{}, sa, sb);
+        if (ti + 1 >= ntiles) break;
+        if (kRenew && __builtin_expect(ti + 1 == renew, 0)) take_reference(sb);
+        round(ti + 1, std::integral_constant<int, 1>{}, sb, sa);
+        if (ti + 2 >= ntiles) break;
+        if (kRenew && __builtin_expect(ti + 2 == renew, 0)) take_reference(sa);
+        round(ti + 2, std::integral_constant<int, 2>{}, sa, sb);
+        if (ti + 3 >= ntiles) break;
+        if (kRenew && __builtin_expect(ti + 3 == renew, 0)) take_reference(sb);
+        round(ti + 3, std::integral_constant<int, 3>{}, sb, sa);
+      }
+      // No load may still be writing LDS when the stages are used again.
+      __builtin_amdgcn_s_waitcnt(wait_vm(0));
+      compiler_fence();
+    }
+    lds_sync();
+
+    // If the pass met a V value above the fp16 range, its result is thrown
+    // away and the range taken again, a tile at a time, with V split by
+    // magnitude into bands (see kBandExp): a band's P.V is added in fp32 to
+    // the accumulators, which then carry 2^kLargeExp. So every row keeps
+    // the precision of the values it sees, whatever the others see.
+    const bool banded = lds.large != 0;
+    if (__builtin_expect(banded, 0)) {
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[dt][i] = 0.f;
       m = ninf;
-      l = 0.f;                     // over this lane's keys; summed across the two halves at the end
-      if (tid == 0) lds.large = 0;
-      lds_sync();
-
-      auto mask = [&](int t0, f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
-        const int d = lim - t0 - 4 * hi;
-#pragma unroll
-        for (int kt = 0; kt < kKT32; ++kt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s[kt][i] = 32 * kt + 8 * (i >> 2) + (i & 3) > d ? ninf : s[kt][i];
-      };
-      auto row_max = [&](const f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
-        float x = ninf;
-#pragma unroll
-        for (int kt = 0; kt < kKT32; ++kt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) x = fmaxf(x, s[kt][i] * c);
-        return max_xor32(x);
-      };
-      // Weight i of the tile: raw score times c is its log2-domain logit.
-      auto weight = [&](const f32x16_t (&s)[kKT32], int i, float mref, f16x8_t (&ph)[2 * kKT32], float (&ps)[4]) __attribute__((always_inline)) {
-        const float pe = fast_exp2(fmaf(s[i >> 4][i & 15], c, -mref));
-        ps[i & 3] += pe;
-        ph[i >> 3][i & 7] = (_Float16)pe;
-      };
-      // Weights of one tile (scores s) interleaved with the scores of the
-      // next (K stage `stage`, into sn): per step two MFMAs, the next step's
-      // operand reads and four weights; the scheduling barriers keep the
-      // order. Returns the sum of the weights over this lane's keys.
-      auto weights_scores = [&](auto stage, const f32x16_t (&s)[kKT32], f32x16_t (&sn)[kKT32], f16x8_t (&ph)[2 * kKT32]) __attribute__((always_inline)) {
-        float ps[4] = {0.f, 0.f, 0.f, 0.f};
-        bf16x8_t ka[2][kKT32];
-        read_k(stage, 0, ka[0]);
-#pragma unroll
-        for (int kt = 0; kt < kKT32; ++kt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) sn[kt][i] = 0.f;
-        __builtin_amdgcn_sched_barrier(0);
-        // The SIMD's other wave, at another point of its round, fills the gaps
-        // instead of delaying the MFMAs (8K prompts 4361 -> 4284 us).
-        __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-          if (ks < 7) read_k(stage, ks + 1, ka[(ks + 1) & 1]);
-#pragma unroll
-          for (int kt = 0; kt < kKT32; ++kt) sn[kt] = mfma32(ka[ks & 1][kt], qb[ks], sn[kt]);
-#pragma unroll
-          for (int i = 2 * kKT32 * ks; i < 2 * kKT32 * (ks + 1); ++i) weight(s, i, m, ph, ps);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_s_setprio(0);
-        return (ps[0] + ps[1]) + (ps[2] + ps[3]);
-      };
-      // One tile: its weights (scores s) with the next tile's scores (sn),
-      // then its P.V, with the conversion of the V of the tile after next.
-      //
-      // Order between the waves, with a barrier before every even tile 2p
-      // only. Rounds 2p and 2p + 1 read K(2p + 1), K(2p + 2), V(2p) and
-      // V(2p + 1); they write V(2p + 2) and V(2p + 3), into the stages last
-      // read in rounds 2p - 2 and 2p - 1, and at the end of round 2p request
-      // K(2p + 3) and K(2p + 4), into the stages last read in the same two
-      // rounds. All these were before the barrier, and what is written is
-      // read after the next one, at which every wave has waited for its own
-      // loads and stores: vmcnt counts in order, and only the two loads of
-      // V(2p + 2), issued after the K loads that are needed, may be pending.
-      // Tiles past the end are requested and converted too (empty
-      // resources: zeros), so the counts never change.
-      auto round = [&](int ti, auto stage, f32x16_t (&s)[kKT32], f32x16_t (&sn)[kKT32]) __attribute__((always_inline)) {
-        constexpr int st = decltype(stage)::value;
-        const int t0 = k0 + ti * kKT;
-        if constexpr (st % 2 == 0) {
-          __builtin_amdgcn_s_waitcnt(wait_vm(kPaged ? 3 : 2));
-          __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-          bare_barrier();
-        }
-        f16x8_t ph[2 * kKT32];
-        __builtin_amdgcn_sched_barrier(0);
-        float ps = weights_scores(std::integral_constant<int, (st + 1) & 3>{}, s, sn, ph);
-        // Rare: move the reference and form the weights again. A row without
-        // one so far (no tile with a finite score) has weights of inf or NaN
-        // and takes this branch too, on every tile until one has.
-        if (__builtin_expect(__any(!(ps <= kMaxWeightSum)), 0)) {
-          const float mn = fmaxf(m, row_max(s));
-          const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
-          m = mn;
-          l *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
-          const float mref = m == ninf ? 0.f : m;
-          float pt[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int i = 0; i < 16 * kKT32; ++i) weight(s, i, mref, ph, pt);
-          ps = (pt[0] + pt[1]) + (pt[2] + pt[3]);
-        }
-        l += ps;
-        if (__builtin_expect(t0 + 2 * kKT > cut, 0)) mask(t0 + kKT, sn);
-        __builtin_amdgcn_sched_barrier(0);
-        f16x8_t va[2][4];
-        read_v(stage, 0, va[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        constexpr int nv = (st + 2) & 3;
-        float vmax = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 2 * kKT32; ++ks) {
-          if (ks < 2 * kKT32 - 1) read_v(stage, ks + 1, va[(ks + 1) & 1]);
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt) o[dt] = mfma32(va[ks & 1][dt], ph[ks], o[dt]);
-          if (ks >= 2 * kKT32 - 2) put_v(nv, ks - (2 * kKT32 - 2), false, vmax);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        if (__builtin_expect(scaled, 0)) {
-          put_v(nv, 0, true, vmax);
-          put_v(nv, 1, true, vmax);
-        } else if (__builtin_expect(__any(!(vmax <= 65504.f)), 0)) {
-          lds.large = 1;
-        }
-        // Here the pages of tiles ti + 3 and ti + 4 have arrived (with the V
-        // pieces converted above, or earlier).
-        const int g3 = page_of(p3), g4 = page_of(p4);
-        if constexpr (st % 2 == 0) {
-          issue_k(ti + 3, (st + 3) & 3, g3);
-          issue_k(ti + 4, st, g4);
-        }
-        p3 = p4;
-        p4 = ask_page(ti + 5);
-        load_v(ti + 3, g3);
-        __builtin_amdgcn_sched_barrier(0);
-      };
-
-      if (ntiles > 0) {
-        f32x16_t sa[kKT32], sb[kKT32];
-        // Pipeline start: everything is requested before anything is used.
-        const int asked[3] = {ask_page(0), ask_page(1), ask_page(2)};
-        p3 = ask_page(3);
-        p4 = ask_page(4);
-        const int pg[3] = {page_of(asked[0]), page_of(asked[1]), page_of(asked[2])};
-        load_v(0, pg[0]);
-        const U4 v0[2] = {vv[0], vv[1]};
-        load_v(1, pg[1]);
-        const U4 v1[2] = {vv[0], vv[1]};
-#pragma unroll
-        for (int t = 0; t < 3; ++t) issue_k(t, t, pg[t]);
-        float vmax = 0.f;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) vv[e] = v0[e];
-        put_v(0, 0, scaled, vmax);
-        put_v(0, 1, scaled, vmax);
-#pragma unroll
-        for (int e = 0; e < 2; ++e) vv[e] = v1[e];
-        put_v(1, 0, scaled, vmax);
-        put_v(1, 1, scaled, vmax);
-        if (!scaled && !(vmax <= 65504.f)) lds.large = 1;
-        load_v(2, pg[2]);
-        __builtin_amdgcn_s_waitcnt(wait_vm(2));
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-        bare_barrier();
-        {
-          bf16x8_t ka[kKT32];
-#pragma unroll
-          for (int kt = 0; kt < kKT32; ++kt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) sa[kt][i] = 0.f;
-#pragma unroll
-          for (int ks = 0; ks < 8; ++ks) {
-            read_k(std::integral_constant<int, 0>{}, ks, ka);
-#pragma unroll
-            for (int kt = 0; kt < kKT32; ++kt) sa[kt] = mfma32(ka[kt], qb[ks], sa[kt]);
-          }
-        }
-        if (k0 + kKT > cut) mask(k0, sa);
-        m = row_max(sa);
-        // The reference taken again, before the weights of tile `renew` are
-        // formed (between two rounds: within one it costs 6 % of a prefill).
-        int renew = (a.ref_keys - k0 % a.ref_keys) / kKT;
-        auto take_reference = [&](const f32x16_t (&s)[kKT32]) __attribute__((always_inline)) {
-          renew += a.ref_keys / kKT;
-          const float x = row_max(s);
-          const float mn = x == ninf ? m : fmaxf(x, m - kRefDown);
-          const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
-          m = mn;
-          l *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
-        };
-        for (int ti = 0; ti < ntiles; ti += 4) {
-          if (kRenew && __builtin_expect(ti == renew, 0)) take_reference(sa);
-          round(ti, std::integral_constant<int, 0>{}, sa, sb);
-          if (ti + 1 >= ntiles) break;
-          if (kRenew && __builtin_expect(ti + 1 == renew, 0)) take_reference(sb);
-          round(ti + 1, std::integral_constant<int, 1>{}, sb, sa);
-          if (ti + 2 >= ntiles) break;
-          if (kRenew && __builtin_expect(ti + 2 == renew, 0)) take_reference(sa);
-          round(ti + 2, std::integral_constant<int, 2>{}, sa, sb);
-          if (ti + 3 >= ntiles) break;
-          if (kRenew && __builtin_expect(ti + 3 == renew, 0)) take_reference(sb);
-          round(ti + 3, std::integral_constant<int, 3>{}, sb, sa);
-        }
-        // No load may still be writing LDS when the stages are used again.
-        __builtin_amdgcn_s_waitcnt(wait_vm(0));
-        compiler_fence();
-      }
-      lds_sync();
-      const bool again = !scaled && lds.large != 0;
-      lds_sync();
-      if (!again) break;
-      // Largest |V| of each dimension over the keys of this range, then the
-      // factors 2^-E_d with max |v| 2^-E_d < 2^16.
-      if (tid < kHeadDim) lds.vmax[tid] = 0u;
-      lds_sync();
+      l = 0.f;
+#pragma unroll 1
       for (int ti = 0; ti < ntiles; ++ti) {
-        load_v(ti, page_of(ask_page(ti)));
+        const int page = page_of(ask_page(ti));
+        issue_k(ti, 0, page);
+        load_v(ti, page);
+        uint32_t has = 0;
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          const float x[8] = {bf_lo(vv[e].x), bf_hi(vv[e].x), bf_lo(vv[e].y), bf_hi(vv[e].y),
-                              bf_lo(vv[e].z), bf_hi(vv[e].z), bf_lo(vv[e].w), bf_hi(vv[e].w)};
+          const uint32_t w[4] = {vv[e].x, vv[e].y, vv[e].z, vv[e].w};
 #pragma unroll
-          for (int i = 0; i < 8; ++i) atomicMax(&lds.vmax[8 * piece_of(e) + i], __float_as_uint(fabsf(x[i])));
+          for (int i = 0; i < 4; ++i) has |= 1u << band_of(w[i] << 16) | 1u << band_of(w[i]);
+        }
+        if ((has & ~1u) != 0) atomicOr(&lds.bands[ti & 1], has);
+        if (tid == 0) lds.bands[(ti + 1) & 1] = 0u;
+        __builtin_amdgcn_s_waitcnt(wait_vm(0));
+        lds_sync();
+        const uint32_t bands = __builtin_amdgcn_readfirstlane(lds.bands[ti & 1]) | 1u;
+        f32x16_t s[kKT32];
+#pragma unroll
+        for (int kt = 0; kt < kKT32; ++kt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[kt][i] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+          bf16x8_t ka[kKT32];
+          read_k(std::integral_constant<int, 0>{}, ks, ka);
+#pragma unroll
+          for (int kt = 0; kt < kKT32; ++kt) s[kt] = mfma32(ka[kt], qb[ks], s[kt]);
+        }
+        if (k0 + (ti + 1) * kKT > cut) mask(k0 + ti * kKT, s);
+        const float mn = fmaxf(m, row_max(s));
+        const float alpha = m == mn ? 1.f : fast_exp2(m - mn);
+        const float mref = mn == ninf ? 0.f : mn;
+        m = mn;
+        f16x8_t ph[2 * kKT32];
+        float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 16 * kKT32; ++i) weight(s, i, mref, ph, ps);
+        l = fmaf(l, alpha, (ps[0] + ps[1]) + (ps[2] + ps[3]));
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+#pragma unroll 1
+        for (int band = 0; band <= 4; ++band) {
+          if (((bands >> band) & 1u) == 0) continue;
+          const float down = exp2_of(-kBandExp * band), back = exp2_of(kBandExp * band + kLargeExp);
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const uint32_t w[4] = {vv[e].x, vv[e].y, vv[e].z, vv[e].w};
+            uint32_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float x0 = band_of(w[i] << 16) == band ? bf_lo(w[i]) * down : 0.f;
+              const float x1 = band_of(w[i]) == band ? bf_hi(w[i]) * down : 0.f;
+              h[i] = __builtin_bit_cast(uint32_t, f16x2_t{(_Float16)x0, (_Float16)x1});
+            }
+            st16(lds.v[0] + (wrow + 4 * e) * kRowBytes + 16 * lane, U4{h[0], h[1], h[2], h[3]});
+          }
+          lds_sync();
+#pragma unroll
+          for (int dt = 0; dt < 4; ++dt) {
+            f32x16_t y;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) y[i] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 2 * kKT32; ++ks) y = mfma32(read_v32(0, ks, dt), ph[ks], y);
+            o[dt] += y * back;
+          }
+          lds_sync();  // read before the next band or tile is written
         }
       }
-      lds_sync();
-      if (tid < kHeadDim) {
-        const int ex = (int)((lds.vmax[tid] >> 23) & 0xff) - 127;  // max |v| < 2^(ex + 1)
-        lds.vscale[tid] = __uint_as_float((uint32_t)(127 - max(ex - 15, 0)) << 23);
-      }
-      scaled = true;
-      lds_sync();
     }
 
     const float lt = sum_xor32(l);
     if (rho < R) {
-      const float inv = lt > 0.f ? 1.f / lt : 0.f;
+      const float inv = lt > 0.f ? (banded ? exp2_of(-kLargeExp) : 1.f) / lt : 0.f;
       const float l2 = lt > 0.f ? m + fast_log2(lt) : ninf;
       const size_t oi = ((size_t)bb * a.q_heads + (size_t)hk * G + rho % G) * f + rho / G;
       float* po = S == 1 ? a.out + oi * kHeadDim
@@ -689,12 +750,8 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
         for (int i4 = 0; i4 < 4; ++i4) {
           const int d = 32 * dt + 8 * i4 + 4 * hi;
-          f32x4_t y = {o[dt][4 * i4] * inv, o[dt][4 * i4 + 1] * inv, o[dt][4 * i4 + 2] * inv, o[dt][4 * i4 + 3] * inv};
-          if (scaled) {  // back to the values' own scale: times 2^E_d
-#pragma unroll
-            for (int i = 0; i < 4; ++i) y[i] *= 1.f / lds.vscale[d + i];
-          }
-          *reinterpret_cast<f32x4_t*>(po + d) = y;
+          *reinterpret_cast<f32x4_t*>(po + d) =
+              f32x4_t{o[dt][4 * i4] * inv, o[dt][4 * i4 + 1] * inv, o[dt][4 * i4 + 2] * inv, o[dt][4 * i4 + 3] * inv};
         }
       if (hi == 0) {
         if (S > 1)

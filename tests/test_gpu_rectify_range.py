@@ -53,3 +53,22 @@ def test_merge_of_the_largest_values(B, H, g, f, L):
     """Whole dimensions of +-3e38: every split's row is close to the largest
     float, and so is their mean."""
     assert rectify(B, H, g, f, L, [(slice(None), 5, 3e38), (slice(None), 77, -3.3e38)], "largest") <= TOL
+
+
+@pytest.mark.parametrize("B,H,g,f,L", [(1, 2, 4, 32, 1100),     # 4 waves, several splits
+                                       (1, 2, 1, 100, 100),     # 4 waves, one split
+                                       (2, 2, 4, 300, 900),     # 8 waves, several splits
+                                       (8, 8, 4, 513, 520)])    # 8 waves, pairs of query blocks
+def test_rows_before_a_large_value(B, H, g, f, L):
+    """Values above the fp16 range at rows of the window that most query rows
+    do not see: those keep the precision of the values they see, also where
+    the large value sits in their own tile, and later rows stay within the
+    bound of what they see. Several magnitudes in one dimension, and a
+    dimension whose large value lies in the cache before the window."""
+    r = L - f
+    plants = [(r + f // 2, 5, 3e38), (r + f // 3, 6, 1e5), (r + 2 * f // 3, 6, -2e20), (L - 1, 7, 3e38),
+              (r + 1, 40, 7e4), (r + 5, 40, -5e30), (r + f // 2 + 1, 41, 2.0 ** 36), (L - 3, 42, -1e9),
+              (r + f // 2, 5 + 64, -65536.0), (r + f // 2 + 2, 100, 65280.0)]
+    if r > 70:
+        plants += [(64, 90, 8e4), (r - 1, 91, -3e38)]
+    assert rectify(B, H, g, f, L, plants, "late") <= TOL
