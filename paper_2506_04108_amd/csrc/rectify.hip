@@ -309,7 +309,10 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
   const bool seq_ok = L >= f && L <= a.c.capacity;
   const int k0 = split * a.chunk;
   const float ninf = -__builtin_inff();
-  const float c = a.scale_log2;
+  // Softmax scale: a negative one negates the queries, zero clears them (the
+  // mask and the row maximum are taken of scores before a positive factor).
+  const float c = a.scale_log2 == 0.f ? 1.f : fabsf(a.scale_log2);
+  const uint32_t q_and = a.scale_log2 == 0.f ? 0u : ~0u, q_xor = a.scale_log2 < 0.f ? 0x80008000u : 0u;
   const int hi = lane >> 5, lq = lane & 31;
 
   // Wave w brings in tile rows 8 w .. + 8: lane i fills slot i % 16 of rows
@@ -384,7 +387,11 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
       lim = min(L - f + r, k1 - 1);
       const uint16_t* qp = a.q_f + (((size_t)bb * a.q_heads + (size_t)hk * G + h) * f + r) * kHeadDim;
 #pragma unroll
-      for (int s = 0; s < 8; ++s) qb[s] = __builtin_bit_cast(bf16x8_t, ld16(qp + 16 * s + 8 * hi));
+      for (int s = 0; s < 8; ++s) {
+        const U4 x = ld16(qp + 16 * s + 8 * hi);
+        qb[s] = __builtin_bit_cast(bf16x8_t, U4{(x.x & q_and) ^ q_xor, (x.y & q_and) ^ q_xor,
+                                               (x.z & q_and) ^ q_xor, (x.w & q_and) ^ q_xor});
+      }
     } else {
 #pragma unroll
       for (int s = 0; s < 8; ++s) qb[s] = __builtin_bit_cast(bf16x8_t, U4{0, 0, 0, 0});

@@ -73,3 +73,19 @@ def test_first_tile_without_a_finite_score(g, f):
     eo, el = max_abs_err(go, ro), max_abs_err(gl, rl)
     print(f"first tile -inf g={g} f={f}: |dO| {eo:.2e} |dlse| {el:.2e}", flush=True)
     assert eo <= 1.2e-3 and el <= 1e-4
+
+
+@pytest.mark.parametrize("sm_scale", [0.0, -0.05, -0.6])
+@pytest.mark.parametrize("g,f", [(4, 32), (4, 65)])
+def test_softmax_scale_of_every_sign(g, f, sm_scale):
+    """Zero and negative softmax scales, which the other calls take too: zero
+    weighs every visible key alike, a negative one prefers the smallest
+    products. Same bound as above."""
+    B, H, L = 2, 2, 1008
+    w = W.TINY_4K.with_(batch=B, num_kv_heads=H, num_q_heads=H * g, seq_len=L, seed_tag=f"sign{f}")
+    K, V = (np.ascontiguousarray(x[:, :, :L]) for x in W.kv_cache(w, capacity=1024))
+    q = W.rectify_inputs(w, 1, K[:, :, L - f:], V[:, :, L - f:], f)[0]
+    go, gl, ro, rl = rectify(K, V, q, f, sm_scale)
+    eo, el = max_abs_err(go, ro), max_abs_err(gl, rl)
+    print(f"sm_scale {sm_scale} g={g} f={f}: |dO| {eo:.2e} |dlse| {el:.2e}", flush=True)
+    assert eo <= 1.2e-3 and el <= 1e-4
