@@ -1,0 +1,63 @@
+"""Workgroups that take two query blocks one after the other (more than 512
+blocks in all), against the oracle on groups picked over the launch: an odd
+number of blocks (the middle one has no partner), head counts on both sides
+of the XCD mapping, ragged lengths, both layouts, and a large V value seen by
+one block of a pair only.
+
+Bound: weights rounded to fp16 (2^-12) times the largest |V| (below 4.9)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2506_04108_amd as R
+import workloads as W
+from gpu_util import i32, make_cache, make_paged_cache, up
+from oracle.compare import max_abs_err
+
+pytestmark = pytest.mark.gpu
+TOL = 1.2e-3
+
+
+@pytest.mark.parametrize("B,H,g,f,lens,paged,big", [
+    (44, 4, 1, 513, [600], False, False),            # 3 blocks, 528 in all
+    (44, 4, 1, 513, [600, 541, 513], True, False),
+    (22, 8, 1, 513, [577, 640], False, False),       # 8 heads: groups spread over the XCDs
+    (11, 8, 2, 700, [700, 733], True, False),        # 6 blocks, 528 in all
+    (44, 4, 1, 513, [513], False, True),             # value in the last block's rows only
+    (44, 4, 1, 513, [600, 530], True, True),
+])
+def test_pairs(B, H, g, f, lens, paged, big):
+    lens = [lens[i % len(lens)] for i in range(B)]
+    cap = -(-max(lens) // 16) * 16
+    w = W.TINY_4K.with_(batch=2, num_kv_heads=H, num_q_heads=H * g, seq_len=cap, seed_tag=f"pairs{f}{H}")
+    # Two sequences' worth of inputs, dealt out: every group has its own order.
+    K2, V2 = W.kv_cache(w, capacity=cap)
+    K = np.stack([np.roll(K2[i % 2], i, axis=0) for i in range(B)])
+    V = np.stack([np.roll(V2[i % 2], i, axis=1) for i in range(B)])
+    if big:
+        for i in range(B):
+            V[i, :, lens[i] - 3, 9] = W.f32_to_bf16_bits(np.array([1e30], np.float32))[0]
+    kf = np.stack([K[i, :, lens[i] - f:lens[i]] for i in range(B)])
+    vf = np.stack([V[i, :, lens[i] - f:lens[i]] for i in range(B)])
+    q2 = W.rectify_inputs(w, 2, K2[:, :, :f], V2[:, :, :f], f)[0]
+    qf = np.stack([np.roll(q2[i % 2], i, axis=0) for i in range(B)])
+    cache = make_paged_cache(K, V, 16, lens, seed=9, sentinel=False) if paged else make_cache(K, V, 16, sentinel=False)
+    lt = i32(lens)
+    out, lse = R.dense_rectify(cache, up(qf), up(kf), up(vf), lt, max(lens))
+    torch.cuda.synchronize()
+    go, gl = out.cpu().numpy(), lse.cpu().numpy()
+    assert np.all(np.isfinite(go))
+    for bi, hi in {(0, 0), (1, H - 1), (B // 2, 1), (B - 1, H - 1)}:
+        L = lens[bi]
+        Kg, Vg = O.bf16_to_f64(K[bi, hi]), O.bf16_to_f64(V[bi, hi])
+        seen = np.maximum.accumulate(np.abs(Vg), axis=0)
+        kmin, kmax = O.block_summaries(Kg, L, 16)
+        q = O.bf16_to_f64(qf[bi, hi * g:(hi + 1) * g])
+        ro, rl = O.rectify_group(q, Kg, Vg, kmin, kmax, L, f, 16, w.sm_scale, Kg[L - f:L].copy(), Vg[L - f:L].copy())
+        scale = np.maximum(1.0, seen[L - f:L] / 4.9)[None]
+        eo = float((np.abs(go[bi, hi * g:(hi + 1) * g] - ro) / scale).max())
+        el = max_abs_err(gl[bi, hi * g:(hi + 1) * g], rl)
+        print(f"pairs B={B} H={H} g={g} f={f} paged={paged} big={big} ({bi},{hi}): |dO| {eo:.2e} |dlse| {el:.2e}",
+              flush=True)
+        assert eo <= TOL and el <= 1e-4
