@@ -217,25 +217,29 @@ __global__ __launch_bounds__(256) void k_rectify_rows(RectifyArgs a) {
   uint16_t* vb = const_cast<uint16_t*>(a.c.v) + (size_t)row0 * kHeadDim + col;
   const uint16_t* kf = a.k_f + (size_t)grp * a.f * kHeadDim + col;
   const uint16_t* vf = a.v_f + (size_t)grp * a.f * kHeadDim + col;
-  U4 rows[BS / 4];
+  // Every row is requested before the first is stored: the stores might alias
+  // the later loads, so the compiler would not move them ahead (a round trip
+  // per four rows otherwise; 64 groups, f = 32: 0.4 us a call).
+  U4 rows[BS / 4], vrows[BS / 4];
 #pragma unroll
   for (int i = 0; i < BS / 4; ++i) {
     const int t = m * BS + r + 4 * i;
-    rows[i] = U4{0, 0, 0, 0};
+    rows[i] = vrows[i] = U4{0, 0, 0, 0};
     if (t < L) {
-      if (t >= first)
+      if (t >= first) {
         rows[i] = ld16(kf + (size_t)(t - first) * kHeadDim);
-      else if (a.refresh)
+        vrows[i] = ld16(vf + (size_t)(t - first) * kHeadDim);
+      } else if (a.refresh) {
         rows[i] = ld16(kb + (size_t)(r + 4 * i) * kHeadDim);
+      }
     }
   }
 #pragma unroll
   for (int i = 0; i < BS / 4; ++i) {
     const int t = m * BS + r + 4 * i;
     if (t < L && t >= first) {
-      const U4 v = ld16(vf + (size_t)(t - first) * kHeadDim);
       st16(kb + (size_t)(r + 4 * i) * kHeadDim, rows[i]);
-      st16(vb + (size_t)(r + 4 * i) * kHeadDim, v);
+      st16(vb + (size_t)(r + 4 * i) * kHeadDim, vrows[i]);
     }
   }
   if (a.refresh) {
@@ -256,7 +260,13 @@ __global__ __launch_bounds__(256) void k_rectify_rows(RectifyArgs a) {
 // their loads are non-temporal (64K rectification 425 -> 414 us, 7B-class 32K
 // 95.1 -> 92.4 us); with several query blocks a group's K and V are read
 // again from L2, and non-temporal loads cost (8K prompts 4201 -> 4311 us).
-template <int kWaves, bool kPaged, bool kNt>
+//
+// kStaged (full windows of 4 waves in several splits): the partial rows go out
+// through LDS, instead of a lane pair's 32 bytes of each row at a time. 64
+// groups of 128 rows over 1500 / 4096 tokens: 40.8 -> 38.5, 53.9 -> 51.9 us.
+// Not with fewer rows (64 rows: 38.4 -> 39.0 us), nor with 8 waves, whose
+// registers spill with it (7B-class 32K, f = 32: 91.9 -> 99.7 us).
+template <int kWaves, bool kPaged, bool kNt, bool kStaged>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_rectify_attn(RectifyArgs a) {
   constexpr int kLoadRows = 8;                   // tile rows whose K and V each wave brings in
   constexpr int kKT = kLoadRows * kWaves;        // keys per tile
@@ -746,20 +756,40 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2, 
     }
 
     const float lt = sum_xor32(l);
-    if (rho < R) {
-      const float inv = lt > 0.f ? (banded ? exp2_of(-kLargeExp) : 1.f) / lt : 0.f;
-      const float l2 = lt > 0.f ? m + fast_log2(lt) : ninf;
-      const size_t oi = ((size_t)bb * a.q_heads + (size_t)hk * G + rho % G) * f + rho / G;
-      float* po = S == 1 ? a.out + oi * kHeadDim
-                         : a.part_o + (((size_t)grp * S + split) * R + rho) * kHeadDim;
+    const float inv = lt > 0.f ? (banded ? exp2_of(-kLargeExp) : 1.f) / lt : 0.f;
+    auto out4 = [&](int dt, int i4) __attribute__((always_inline)) {
+      return f32x4_t{o[dt][4 * i4] * inv, o[dt][4 * i4 + 1] * inv, o[dt][4 * i4 + 2] * inv, o[dt][4 * i4 + 3] * inv};
+    };
+    if constexpr (kStaged) {
+      // The wave's 32 rows through its share of the tile stages, two whole
+      // 512-byte rows to a store; 16-byte piece p of row r sits in slot p ^ r.
+      static_assert(sizeof(lds.k) + sizeof(lds.v) >= kRowsPerWg * kHeadDim * 4, "a wave's share of the stages");
+      uint8_t* buf = &lds.k[0][0] + wave * (kRowsPerWave * kHeadDim * 4);
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int d = 32 * dt + 8 * i4 + 4 * hi;
-          *reinterpret_cast<f32x4_t*>(po + d) =
-              f32x4_t{o[dt][4 * i4] * inv, o[dt][4 * i4 + 1] * inv, o[dt][4 * i4 + 2] * inv, o[dt][4 * i4 + 3] * inv};
-        }
+        for (int i4 = 0; i4 < 4; ++i4)
+          *reinterpret_cast<f32x4_t*>(buf + lq * (kHeadDim * 4) + 16 * ((8 * dt + 2 * i4 + hi) ^ lq)) = out4(dt, i4);
+      compiler_fence();  // a wave's LDS accesses run in order
+      float* po = a.part_o + (((size_t)grp * S + split) * R + row_base) * kHeadDim + 4 * lq;
+#pragma unroll 4
+      for (int j = 0; j < kRowsPerWave / 2; ++j) {
+        const int r = 2 * j + hi;
+        const f32x4_t y = *reinterpret_cast<const f32x4_t*>(buf + r * (kHeadDim * 4) + 16 * (lq ^ r));
+        if (row_base + r < R) *reinterpret_cast<f32x4_t*>(po + r * kHeadDim) = y;
+      }
+    }
+    if (rho < R) {
+      const float l2 = lt > 0.f ? m + fast_log2(lt) : ninf;
+      const size_t oi = ((size_t)bb * a.q_heads + (size_t)hk * G + rho % G) * f + rho / G;
+      if constexpr (!kStaged) {
+        float* po = S == 1 ? a.out + oi * kHeadDim
+                           : a.part_o + (((size_t)grp * S + split) * R + rho) * kHeadDim;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int i4 = 0; i4 < 4; ++i4) *reinterpret_cast<f32x4_t*>(po + 32 * dt + 8 * i4 + 4 * hi) = out4(dt, i4);
+      }
       if (hi == 0) {
         if (S > 1)
           a.part_lse[((size_t)grp * S + split) * R + rho] = l2;
@@ -941,24 +971,26 @@ hipError_t launch_rectify(const RectifyArgs& a, hipStream_t stream) {
   const int groups = a.c.batch * a.c.kv_heads;
   const dim3 grid(a.num_splits * rectify_items(groups, a.num_qblocks) * groups);
   const bool paged = a.c.table != nullptr;
-  auto launch = [&](auto waves, auto nt) {
+  auto launch = [&](auto waves, auto nt, auto staged) {
     constexpr int W = decltype(waves)::value;
-    constexpr bool N = decltype(nt)::value;
+    constexpr bool N = decltype(nt)::value, P = decltype(staged)::value;
     if (paged)
-      hipLaunchKernelGGL((k_rectify_attn<W, true, N>), grid, dim3(64 * W), 0, stream, a);
+      hipLaunchKernelGGL((k_rectify_attn<W, true, N, P>), grid, dim3(64 * W), 0, stream, a);
     else
-      hipLaunchKernelGGL((k_rectify_attn<W, false, N>), grid, dim3(64 * W), 0, stream, a);
+      hipLaunchKernelGGL((k_rectify_attn<W, false, N, P>), grid, dim3(64 * W), 0, stream, a);
   };
-  if (waves_for_rows(a.group * a.f) == 4)
-    launch(std::integral_constant<int, 4>{}, std::true_type{});
+  const int rows = a.group * a.f;
+  if (waves_for_rows(rows) == 4 && rows > 3 * kRowsPerWave && a.num_splits > 1)
+    launch(std::integral_constant<int, 4>{}, std::true_type{}, std::true_type{});
+  else if (waves_for_rows(rows) == 4)
+    launch(std::integral_constant<int, 4>{}, std::true_type{}, std::false_type{});
   else if (a.num_qblocks == 1)
-    launch(std::integral_constant<int, 8>{}, std::true_type{});
+    launch(std::integral_constant<int, 8>{}, std::true_type{}, std::false_type{});
   else
-    launch(std::integral_constant<int, 8>{}, std::false_type{});
+    launch(std::integral_constant<int, 8>{}, std::false_type{}, std::false_type{});
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.num_splits == 1) return hipSuccess;  // the attention kernel wrote out / lse
-  const int rows = a.group * a.f;
   if (a.num_splits <= 16)
     hipLaunchKernelGGL(k_rectify_combine<1>, dim3((rows + 3) / 4, groups), dim3(256), 0, stream, a);
   else
