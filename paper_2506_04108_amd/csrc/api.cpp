@@ -293,7 +293,7 @@ int select_common(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
                   const int32_t* seq_lens, int32_t sel_len, const resa_select_params_t* params,
                   int32_t* block_idx, int32_t* num_sel, int32_t n_cap, float* scores_out,
                   void* workspace, size_t workspace_bytes, const void* k_new, const void* v_new,
-                  const SelectLayout& lay, bool step, void* stream, const char* what) {
+                  const SelectLayout& lay, void* stream, const char* what) {
   int32_t group = 0;
   if (int e = check_heads(c, num_q_heads, &group)) return e;
   RESA_CHECK_PTR(q, 16);
@@ -338,7 +338,6 @@ int select_common(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
   a.hist = reinterpret_cast<uint32_t*>(ws + lay.hist);
   a.blocks_per_wg = resa::select_blocks_per_wg(c->batch, c->num_kv_heads, mseq);
   a.fused = mseq <= resa::select_fused_max_blocks() ? 1 : 0;
-  a.lists = step ? 1 : 0;
   a.k_new = static_cast<const uint16_t*>(k_new);
   a.v_new = static_cast<const uint16_t*>(v_new);
   a.lens_out = const_cast<int32_t*>(seq_lens);
@@ -366,7 +365,7 @@ int resa_select_blocks(const resa_kv_cache_t* c, const void* q, int32_t num_q_he
                 c->capacity);
   return select_common(c, q, num_q_heads, seq_lens, max_seq_len, params, block_idx, num_sel, n_cap,
                        scores_out, workspace, workspace_bytes, nullptr, nullptr,
-                       select_layout(c->batch, c->num_kv_heads, max_seq_len, c->block_size), false, stream,
+                       select_layout(c->batch, c->num_kv_heads, max_seq_len, c->block_size), stream,
                        "resa_select_blocks launch");
 }
 
@@ -384,7 +383,7 @@ int resa_append_select(const resa_kv_cache_t* c, const void* k_new, const void* 
                 c->capacity);
   return select_common(c, q, num_q_heads, seq_lens, max_seq_len + 1, params, block_idx, num_sel,
                        n_cap, scores_out, workspace, workspace_bytes, k_new, v_new,
-                       select_layout(c->batch, c->num_kv_heads, max_seq_len + 1, c->block_size), false, stream,
+                       select_layout(c->batch, c->num_kv_heads, max_seq_len + 1, c->block_size), stream,
                        "resa_append_select launch");
 }
 
@@ -624,7 +623,7 @@ int resa_decode_step(const resa_kv_cache_t* c, const void* k_new, const void* v_
   char* ws = static_cast<char*>(workspace);
   // Every argument is checked: the two launches follow.
   if (int e = select_common(c, q, num_q_heads, seq_lens, sel_len, params, block_idx, num_sel, n_cap, nullptr,
-                            ws, workspace_bytes, k_new, v_new, lay.s, true, stream, "resa_decode_step launch"))
+                            ws, workspace_bytes, k_new, v_new, lay.s, stream, "resa_decode_step launch"))
     return e;
   return decode_launch(c, q, num_q_heads, seq_lens, block_idx, num_sel, n_cap, group, splits, sm_scale, out, lse,
                        ws, lay.d, false, stream, "resa_decode_step launch");

@@ -93,7 +93,6 @@ struct SelectArgs {
   uint32_t* counters;          // [B, Hkv], zero between calls
   int32_t blocks_per_wg;
   int32_t fused;               // top-n in the scoring kernel's last workgroup
-  int32_t lists;               // in-window lists from 8193 blocks on (decode step), not from 12289
   // Append fused in front of the selection (null k_new: plain selection).
   const uint16_t* k_new;       // [B, Hkv, D] key of the new token
   const uint16_t* v_new;       // [B, Hkv, D] value of the new token

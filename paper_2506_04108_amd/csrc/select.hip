@@ -302,11 +302,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
     // the top-n of the last workgroup dominates, and half the waves share
     // the CU's SIMDs (4K batch 1 selection 9.9 -> 9.35 us, 32K batch 4
     // 14.2 -> 13.9 us; 64K batch 8, with 1024-block ranges, is slower so).
-    // The decode step's workspace counts the calls that finish on the
-    // in-window path, from 8193 blocks on: there it takes 16 keys per thread,
-    // which have the path (8750 blocks, 16 groups: 22.5 us against 20.6).
-    int per = (a.max_blocks_seq + kSelThreads - 1) / kSelThreads;
-    if (a.lists && per > 8 && per < 16) per = 16;
+    const int per = (a.max_blocks_seq + kSelThreads - 1) / kSelThreads;
     const int per_half = (a.max_blocks_seq + 511) / 512;
     const bool half = a.blocks_per_wg <= 256 && per_half <= 8;
     if (half && per_half <= 4)

@@ -82,19 +82,18 @@ def test_step_matches_separate_calls(g, b):
         pass
 
 
-def test_step_window_lists():
-    """16 groups of 8200 - 8750 blocks (32 keys per thread of the fused
-    step's 512-thread top-n, 31 score ranges of 288 blocks) at sparsity 0.95
-    (n = 411 - 438, so the list entries the path needs fit the 512 threads):
-    from the second step on, the window hint is set and the fused step's top-n
-    takes the in-window path (above-window bits and in-window lists written by
-    its score ranges; the workspace counter of such calls must grow), while
-    append_select (12 keys per thread) reads every key; the selections must be
-    identical and the outputs equal up to summation order."""
-    w = W.LONG_64K.with_(batch=2, num_kv_heads=8, num_q_heads=32, seq_len=140000, sparsity=0.95,
+@pytest.mark.parametrize("lens", [[140000, 131500], [200000]])
+def test_step_window_lists(lens):
+    """Long groups at sparsity 0.95: the step selects as append_select does,
+    with the same counter of calls that finished on the in-window path (its
+    hint set from the second step on). 16 groups of 8200 - 8750 blocks take 12
+    keys per thread, which read every key; 8 groups of 12500 blocks (16 keys
+    per thread, above-window bits and in-window lists written by 32 score
+    ranges; n = 625 list entries fit the 1024 threads) take the path."""
+    B = len(lens)
+    w = W.LONG_64K.with_(batch=B, num_kv_heads=8, num_q_heads=32, seq_len=max(lens), sparsity=0.95,
                          seed_tag="steplists")
-    cap = 140064
-    lens = [140000, 131500]
+    cap = max(lens) + 64
     K, V = W.kv_cache(w, capacity=cap)
     cache = make_cache(K, V, 16, sentinel=False)
     del K, V
@@ -102,9 +101,11 @@ def test_step_window_lists():
     keep = {}
     for _ in run_pair(w, cache, lens, steps=4, keep=keep):
         pass
-    stats = select_stats(keep["step"], 2, 8, step=True)
+    stats = select_stats(keep["step"], B, 8, step=True)
     print(f"in-window top-n calls per group: {stats.ravel().tolist()}", flush=True)
-    assert stats.sum() > 0, "the fused step never took the in-window path"
+    assert np.array_equal(stats, select_stats(keep["select"], B, 8))
+    if max(lens) > 12288 * 16:
+        assert stats.sum() > 0, "the in-window top-n path was not taken"
 
 
 def test_step_against_oracle_loop():
