@@ -162,11 +162,10 @@ size_t resa_select_workspace_size(int32_t batch, int32_t num_kv_heads,
  * >= resa_num_selected(ceil(max_seq_len / block_size), ...) (else
  * RESA_ERR_CAPACITY). scores_out (optional, may be NULL): fp32 [batch,
  * num_kv_heads, ceil(max_seq_len / block_size)], receives the Eq. 4 scores
- * before local forcing (entries past M_b are not written); the workspace
- * keeps the blocks' order-preserving keys either way.
+ * before local forcing (entries past M_b are not written).
  * One kernel scores the blocks and, in the last workgroup of each group to
- * finish, selects them (groups of more than 32768 blocks use a second
- * kernel). The workspace starts with one ticket per group: zero-fill it
+ * finish, selects them (groups of up to 320 blocks are scored and selected by
+ * one workgroup each; groups of more than 32768 blocks use a second kernel). The workspace starts with one ticket per group: zero-fill it
  * before its first use (resa_workspace_clear); every call leaves the tickets
  * at zero again. It also keeps, per group, a hint from the previous call
  * (which bits of the scores to count twice); the hint never changes the
@@ -306,14 +305,13 @@ size_t resa_step_workspace_size(int32_t batch, int32_t num_kv_heads, int32_t num
  * is enqueued.
  * Two kernels, the selection's and the decode's (one persistent kernel that
  * claimed both kinds of work measured 94 against 70 us at 64K batch 8 and 31
- * against 18 us at 4K). The workspace (resa_step_workspace_size) holds a
- * status area, what the selection and the decode keep from call to call (at
- * offsets that follow from the batch and the head count) and their scratch:
- * zero-fill it before its first use (resa_workspace_clear); every call leaves
- * it ready for the next, of this or another length, n_cap or split count.
+ * against 18 us at 4K). The workspace (resa_step_workspace_size) holds what
+ * the selection and the decode keep from call to call (at offsets that follow
+ * from the batch and the head count) and their scratch: zero-fill it before
+ * its first use (resa_workspace_clear); every call leaves it ready for the
+ * next, of this or another length, n_cap or split count. Its first 256 bytes
+ * are reserved and stay zero.
  * Calls sharing a workspace must be ordered on one stream.
- * Status: the uint32 at byte offset 12 of the workspace is 0 after every call
- * (reserved for a launch that could not finish).
  */
 int resa_decode_step(const resa_kv_cache_t* c, const void* k_new, const void* v_new,
                      const void* q, int32_t num_q_heads, int32_t* seq_lens, int32_t max_seq_len,

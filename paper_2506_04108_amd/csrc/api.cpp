@@ -153,6 +153,8 @@ struct DecodeLayout {
   size_t counters, epochs, flags, lse, o, total;
 };
 
+constexpr int32_t kMaxSplits = 256;  // largest num_splits
+
 DecodeLayout decode_layout(int32_t batch, int32_t kv_heads, int32_t group, int32_t splits) {
   DecodeLayout d;
   const size_t groups = (size_t)batch * kv_heads;
@@ -165,16 +167,15 @@ DecodeLayout decode_layout(int32_t batch, int32_t kv_heads, int32_t group, int32
   return d;
 }
 
-// Workspace of resa_decode_step: a status area (words 0 .. 63 and one word per
-// group, always zero), then what the selection and the decode keep from call
-// to call (tickets, window hints, counters; merge tickets and call counts) at
+// Workspace of resa_decode_step: 256 reserved bytes (never written, so zero),
+// then what the selection and the decode keep from call to call (tickets,
+// window hints, counters; merge tickets, call counts and ready flags) at
 // offsets that follow from the batch and the head count alone, then the
-// decode's flags and partials and the selection's scratch, whose sizes follow
-// the split count and the length: a workspace sized for the longest context
-// serves calls of any shorter one, in any order. (The decode's flags lie in
-// front of its partials and of the keys, as in its own workspace: a flag
-// matches only this call's tag, a small call count above the split count,
-// which neither partials nor keys look like.)
+// decode's partials and the selection's scratch, whose sizes follow the split
+// count and the length: a workspace sized for the longest context serves calls
+// of any shorter one, in any order. The flags have room for the largest split
+// count, so nothing else is ever written where a call may look for one (the
+// packed digit counts, for one, can look like a call's tag).
 struct StepLayout {
   SelectLayout s;
   DecodeLayout d;
@@ -187,7 +188,7 @@ StepLayout step_layout(int32_t batch, int32_t kv_heads, int32_t group, int32_t s
   const size_t groups = (size_t)batch * kv_heads;
   const SelectLayout s = select_layout(batch, kv_heads, sel_len, block_size);
   const DecodeLayout d = decode_layout(batch, kv_heads, group, splits);
-  const size_t sel = 256 + round256(groups * 4);
+  const size_t sel = 256;
   l.s.counters = sel + s.counters;
   l.s.seq_counters = sel + s.seq_counters;
   l.s.window = sel + s.window;
@@ -196,7 +197,7 @@ StepLayout step_layout(int32_t batch, int32_t kv_heads, int32_t group, int32_t s
   l.d.counters = dec + d.counters;
   l.d.epochs = dec + d.epochs;
   l.d.flags = dec + round256(d.flags);
-  l.d.lse = l.d.flags + round256(d.lse - d.flags);
+  l.d.lse = l.d.flags + groups * kMaxSplits * 8;
   l.d.o = l.d.lse + (d.o - d.lse);
   l.d.total = l.d.o + round256(d.total - d.o);
   l.s.keys = l.d.total;
@@ -431,8 +432,8 @@ int decode_check(const resa_kv_cache_t* c, const void* q, int32_t num_q_heads,
   RESA_CHECK_PTR(out, 4);
   if (lse != nullptr && !aligned(lse, 4)) return fail(RESA_ERR_INVALID_ARG, "lse is not 4-byte aligned");
   if (n_cap < 0) return fail(RESA_ERR_INVALID_ARG, "n_cap %d < 0", n_cap);
-  if (num_splits < 0 || num_splits > 256)
-    return fail(RESA_ERR_INVALID_ARG, "num_splits %d outside [0, 256]", num_splits);
+  if (num_splits < 0 || num_splits > kMaxSplits)
+    return fail(RESA_ERR_INVALID_ARG, "num_splits %d outside [0, %d]", num_splits, kMaxSplits);
   if (!std::isfinite(sm_scale)) return fail(RESA_ERR_INVALID_ARG, "sm_scale is not finite");
   *splits = num_splits > 0 ? num_splits
                            : resa::decode_auto_splits(c->batch, c->num_kv_heads, n_cap, c->block_size);
@@ -600,8 +601,8 @@ int resa_decode_step(const resa_kv_cache_t* c, const void* k_new, const void* v_
   if (params->min_blocks < 0 || params->n_local < 0)
     return fail(RESA_ERR_INVALID_ARG, "min_blocks (%d) and n_local (%d) must be >= 0",
                 params->min_blocks, params->n_local);
-  if (num_splits < 0 || num_splits > 256)
-    return fail(RESA_ERR_INVALID_ARG, "num_splits %d outside [0, 256]", num_splits);
+  if (num_splits < 0 || num_splits > kMaxSplits)
+    return fail(RESA_ERR_INVALID_ARG, "num_splits %d outside [0, %d]", num_splits, kMaxSplits);
   if (!std::isfinite(sm_scale)) return fail(RESA_ERR_INVALID_ARG, "sm_scale is not finite");
   const int32_t sel_len = max_seq_len + 1;
   const int32_t mseq = (sel_len + c->block_size - 1) / c->block_size;

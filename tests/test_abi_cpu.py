@@ -204,6 +204,18 @@ def test_product_never_imports_oracle():
                 assert "import oracle" not in text and "from oracle" not in text, fn
 
 
+@pytest.mark.parametrize("batch,heads,g", [(1, 1, 1), (2, 4, 7), (8, 8, 4)])
+def test_step_workspace_keeps_flags_apart(batch, heads, g):
+    """The step's workspace has room for the ready flags of the largest split
+    count whatever the call's own, so no scratch of one call ever lies where
+    another looks for a flag: sizes for 1 and 256 splits differ by the
+    partials alone (lse and 128 floats a row, padded to 256 bytes)."""
+    size = lambda s: L.lib().resa_step_workspace_size(batch, heads, heads * g, 6000, 16, 38, s)  # noqa: E731
+    pad = lambda x: -(-x // 256) * 256  # noqa: E731
+    rows = batch * heads * g
+    assert size(256) - size(1) == pad(256 * rows * 4) - pad(rows * 4) + 255 * rows * 512
+
+
 def test_workspace_sizes_grow_with_length():
     """A workspace sized for a longer context serves every shorter one: the
     selection, decode, fused-step and rectification sizes never decrease as
