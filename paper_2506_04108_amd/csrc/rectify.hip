@@ -219,20 +219,15 @@ __global__ __launch_bounds__(256) void k_rectify_rows(RectifyArgs a) {
   const uint16_t* vf = a.v_f + (size_t)grp * a.f * kHeadDim + col;
   // Every row is requested before the first is stored: the stores might alias
   // the later loads, so the compiler would not move them ahead (a round trip
-  // per four rows otherwise; 64 groups, f = 32: 0.4 us a call).
+  // per four rows otherwise; 64 groups, f = 32: 0.4 us a call). And without a
+  // branch around any: a row outside the window takes its K from the cache
+  // (the block lies in it whole) and an edge row's V, which is not used.
   U4 rows[BS / 4], vrows[BS / 4];
 #pragma unroll
   for (int i = 0; i < BS / 4; ++i) {
     const int t = m * BS + r + 4 * i;
-    rows[i] = vrows[i] = U4{0, 0, 0, 0};
-    if (t < L) {
-      if (t >= first) {
-        rows[i] = ld16(kf + (size_t)(t - first) * kHeadDim);
-        vrows[i] = ld16(vf + (size_t)(t - first) * kHeadDim);
-      } else if (a.refresh) {
-        rows[i] = ld16(kb + (size_t)(r + 4 * i) * kHeadDim);
-      }
-    }
+    rows[i] = ld16(t >= first && t < L ? kf + (size_t)(t - first) * kHeadDim : kb + (size_t)(r + 4 * i) * kHeadDim);
+    vrows[i] = ld16(vf + (size_t)min(max(t - first, 0), a.f - 1) * kHeadDim);
   }
 #pragma unroll
   for (int i = 0; i < BS / 4; ++i) {
