@@ -881,35 +881,6 @@ int32_t rectify_num_qblocks(int32_t group, int32_t f) {
   return (rows + per - 1) / per;
 }
 
-// Key splits per group the attention aims for. Short windows (4 waves, two
-// workgroups per CU): about 512 workgroups in all (64K batch 8: 527 us with
-// 256, 414 with 512, 433 with 1024). Long windows (8 waves, one workgroup per
-// CU, W workgroups per split): as many splits as fill the 256 CUs once
-// (7B-class 32K, f = 32, W = 16: 95.1 us with 16 splits, 115.3 with 32). From
-// W = 64 on, the count whose last round is fullest, against what each split
-// adds (a share of a round for the partials' stores and the merge, from
-// W = 224 measured at 1 / 2 / 3 / 4 / 8 splits: 1732 / 1825 / 1875 / 1915 /
-// 1890 us). With a sequence mask, two rounds: the workgroups of sequences
-// left out end at once (2 sequences of 92K, one left out, R = 512: 146 us
-// against 197 with one round).
-static int64_t rectify_target_splits(int32_t batch, int32_t kv_heads, int32_t rows, bool masked) {
-  const int64_t groups = (int64_t)batch * kv_heads;
-  if (waves_for_rows(rows) == 4) return (512 + groups - 1) / groups;
-  const int32_t per = kRowsPerWave * 8;
-  const int64_t W = groups * rectify_items((int)groups, (rows + per - 1) / per);
-  if (W >= kCus) return 1;
-  if (masked) return (2 * kCus + W - 1) / W;
-  if (W <= kCus / 4) return kCus / W;
-  int64_t best = 1, best_cost = 1000;  // thousandths of one round
-  for (int64_t s = 2; s * W <= 2 * kCus; ++s) {
-    const int64_t cost = 1000 * ((W * s + kCus - 1) / kCus) / s + 40 + 20 * (s - 1) * W / kCus;
-    if (cost < best_cost) {
-      best = s;
-      best_cost = cost;
-    }
-  }
-  return best;
-}
 // Short caches still fill the chip (4K, batch 1: 32 splits of 128 keys,
 // 30.4 against 34.0 us per call with a 512-key minimum).
 constexpr int kMinRectChunk = 128;
@@ -918,14 +889,10 @@ static int32_t chunk_for(int64_t target, int32_t max_seq_len) {
   int64_t chunk = (max_seq_len + target - 1) / target;
   chunk = (chunk + kMaxKeyTile - 1) / kMaxKeyTile * kMaxKeyTile;
   if (chunk < kMinRectChunk) chunk = kMinRectChunk;
-  // At most kMaxRectSplits splits (the targets above stay below it).
+  // At most kMaxRectSplits splits (the targets below stay below it).
   const int64_t least = ((int64_t)max_seq_len + kMaxRectSplits - 1) / kMaxRectSplits;
   if (chunk < least) chunk = (least + kMaxKeyTile - 1) / kMaxKeyTile * kMaxKeyTile;
   return (int32_t)chunk;
-}
-
-int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked) {
-  return chunk_for(rectify_target_splits(batch, kv_heads, rows, masked), max_seq_len);
 }
 
 // Keys a softmax reference serves, at most: those of a split when the query
@@ -937,18 +904,74 @@ int32_t rectify_ref_keys(int32_t batch, int32_t kv_heads, int32_t rows, int32_t 
   return chunk_for((512 + wgs - 1) / wgs, max_seq_len);
 }
 
+// Key splits per group at most, whatever the length: about 512 workgroups in
+// all for short windows (4 waves, two workgroups per CU; 64K batch 8: 527 us
+// with 256, 414 with 512, 433 with 1024), up to two rounds of workgroups for
+// long ones (8 waves, one per CU), one split where a round is full anyway.
+static int64_t rectify_most_splits(int32_t batch, int32_t kv_heads, int32_t rows, int64_t* wgs) {
+  const int64_t groups = (int64_t)batch * kv_heads;
+  const int32_t per = waves_for_rows(rows) * kRowsPerWave;
+  *wgs = groups * rectify_items((int)groups, (rows + per - 1) / per);  // workgroups per split
+  if (waves_for_rows(rows) == 4) return (2 * kCus + groups - 1) / groups;
+  return *wgs >= kCus ? 1 : (2 * kCus + *wgs - 1) / *wgs;
+}
+
+// Time of a split count for long windows, in nanoseconds, from what single
+// query blocks measured: a first round 17 us and a later one 14 beside its
+// 64-key tiles, a tile 1.4 us and more as more CUs run at once, and the partial
+// rows and their merge 1 us and a share per workgroup. Fitted to 503 shapes (1
+// to 4 query blocks a group, 4 and 7 heads, 4 to 248 workgroups per split, 260
+// to 32768 keys, 1 to 64 splits).
+static int64_t rectify_cost(int64_t wgs_per_split, int32_t chunk, int32_t max_seq_len) {
+  const int64_t splits = (max_seq_len + chunk - 1) / chunk, wgs = wgs_per_split * splits;
+  const int64_t rounds = (wgs + kCus - 1) / kCus;
+  const int64_t cost = 17000 + 14000 * (rounds - 1) +
+                       rounds * (chunk / kMaxKeyTile) * (1400 + 2 * (wgs < kCus ? wgs : kCus));
+  return splits == 1 ? cost : cost + 1000 + 80 * (wgs < kCus / 2 ? wgs : kCus / 2) + 20 * wgs;
+}
+
+// Long windows: as many splits as fill the 256 CUs once (7B-class 32K, f = 32,
+// 16 workgroups per split: 95.1 us with 16 splits, 115.3 with 32), or the count
+// that rectify_cost puts at least a twentieth lower: one split where the cache
+// is short, a fuller last round where it is long. Over the fitted shapes the
+// count taken is 0.8 % off the best on average and 11 % at most (without the
+// second part 11 % and up to twice: 64 workgroups over 400 keys 38.2 us, 29.2
+// in one split; 160 over 1200 81.4 and 52.1). With a sequence mask, two rounds
+// (the workgroups of sequences left out end at once; 2 sequences of 92K, one
+// left out, R = 512: 146 us against 197 with one round) or one split, compared
+// for half of the workgroups.
+int32_t rectify_chunk(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len, bool masked) {
+  int64_t W;
+  const int64_t most = rectify_most_splits(batch, kv_heads, rows, &W);
+  if (waves_for_rows(rows) == 4 || most == 1) return chunk_for(most, max_seq_len);
+  // A split holds at most eight ranges of a softmax reference (see kRefDown).
+  const int64_t longest = 8 * (int64_t)rectify_ref_keys(batch, kv_heads, rows, max_seq_len);
+  int32_t best = chunk_for(masked ? most : kCus / W, max_seq_len), last = 0;
+  if (masked) W = (W + 1) / 2;
+  int64_t least = rectify_cost(W, best, max_seq_len) * 19 / 20;
+  for (int64_t s = 1; s <= (masked ? 1 : most) && last != kMinRectChunk; s += 1 + s / 32) {
+    const int32_t chunk = chunk_for(s, max_seq_len);
+    if (chunk > longest || chunk == last) continue;
+    last = chunk;
+    const int64_t cost = rectify_cost(W, chunk, max_seq_len);
+    if (cost < least) {
+      best = chunk;
+      least = cost;
+    }
+  }
+  return best;
+}
+
 int32_t rectify_max_splits(int32_t batch, int32_t kv_heads, int32_t rows, int32_t max_seq_len) {
-  // ceil(L / chunk) with chunk >= 128 and chunk >= ceil(L / target) (target
-  // <= 512 < kMaxRectSplits): at most min(ceil(L / 128), target), a bound
-  // that never decreases as L grows, while the split count itself can (the
-  // chunk is rounded up to whole 64-key tiles: 512 splits at L = 65536, 342
-  // at 65537 for one group and one query block).
+  // ceil(L / chunk) with chunk >= 128 and chunk >= ceil(L / most) (most <= 512
+  // < kMaxRectSplits): at most min(ceil(L / 128), most), a bound that never
+  // decreases as L grows, while the split count itself can (the chunk is
+  // rounded up to whole 64-key tiles: 512 splits at L = 65536, 342 at 65537
+  // for one group and one query block).
+  int64_t W;
   const int64_t by_len = ((int64_t)max_seq_len + kMinRectChunk - 1) / kMinRectChunk;
-  // The larger of the two counts, so one size serves masked calls too.
-  const int64_t all = rectify_target_splits(batch, kv_heads, rows, false);
-  const int64_t some = rectify_target_splits(batch, kv_heads, rows, true);
-  const int64_t target = all > some ? all : some;
-  const int64_t s = by_len < target ? by_len : target;
+  const int64_t most = rectify_most_splits(batch, kv_heads, rows, &W);
+  const int64_t s = by_len < most ? by_len : most;
   return (int32_t)(s < 1 ? 1 : s);
 }
 
