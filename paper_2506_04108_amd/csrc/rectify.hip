@@ -221,7 +221,8 @@ __global__ __launch_bounds__(256) void k_rectify_rows(RectifyArgs a) {
   // the later loads, so the compiler would not move them ahead (a round trip
   // per four rows otherwise; 64 groups, f = 32: 0.4 us a call). And without a
   // branch around any: a row outside the window takes its K from the cache
-  // (the block lies in it whole) and an edge row's V, which is not used.
+  // (the block lies in it whole) and an edge row's V, which is not used (blocks
+  // of 64 tokens, 4K batch 1, f = 16: 26.7 -> 24.0 us a call).
   U4 rows[BS / 4], vrows[BS / 4];
 #pragma unroll
   for (int i = 0; i < BS / 4; ++i) {
@@ -934,9 +935,9 @@ static int64_t rectify_cost(int64_t wgs_per_split, int32_t chunk, int32_t max_se
 // 16 workgroups per split: 95.1 us with 16 splits, 115.3 with 32), or the count
 // that rectify_cost puts at least a twentieth lower: one split where the cache
 // is short, a fuller last round where it is long. Over the fitted shapes the
-// count taken is 0.8 % off the best on average and 11 % at most (without the
-// second part 11 % and up to twice: 64 workgroups over 400 keys 38.2 us, 29.2
-// in one split; 160 over 1200 81.4 and 52.1). With a sequence mask, two rounds
+// count taken is 0.8 % off the best on average and 11 % at most (one full
+// round whatever the length: 5.5 and 59 %; 64 workgroups over 400 keys 38.2 us,
+// 29.2 in one split; 128 over 260 45.4 and 29.0). With a sequence mask, two rounds
 // (the workgroups of sequences left out end at once; 2 sequences of 92K, one
 // left out, R = 512: 146 us against 197 with one round) or one split, compared
 // for half of the workgroups.

@@ -4,7 +4,8 @@ number of blocks (the middle one has no partner), head counts on both sides
 of the XCD mapping, ragged lengths, both layouts, and a large V value seen by
 one block of a pair only.
 
-Bound: weights rounded to fp16 (2^-12) times the largest |V| (below 4.9)."""
+Bound: weights rounded to fp16 (2^-12; below 2^-14 of the softmax reference by
+2^-25 of it) times the largest |V| (below 4.9)."""
 import numpy as np
 import pytest
 import torch

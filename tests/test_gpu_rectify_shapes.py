@@ -1,11 +1,16 @@
 """Rectification at the edges of its tiles and of its workgroup choice,
-against the oracle: windows of 127 .. 129 and 255 .. 513 rows (4 and 8 waves,
-odd and even numbers of query blocks), lengths around the 32- and 64-key tiles
-and the splits' ends, both layouts, and logits that climb along the sequence
-(the softmax reference has to move).
+against the oracle: windows of 1 .. 129 and 255 .. 777 rows (4 and 8 waves, one
+to four query blocks a group, each a workgroup of its own; two blocks a
+workgroup are test_gpu_rectify_pairs.py's), lengths around the 32- and 64-key
+tiles and the splits' ends, both layouts, and logits that climb along the
+sequence (the softmax reference has to move).
 
-Bound: a weight is rounded to fp16 (relative 2^-12), so an output is off by at
-most 2^-12 of its dimension's largest |V| (below 4.9 here): 1.2e-3."""
+Bound: a weight is rounded to fp16, by 2^-12 of itself from 2^-14 of the softmax
+reference on and by at most 2^-25 of the reference below (fp16's subnormals),
+and the weights sum to at least the reference. An output is off by at most
+2^-12 of its dimension's largest |V| (below 4.9 here), 1.2e-3, and by 2^-25 of
+it for every key of such a small weight (3e-4 if all of 2000 were): rounding
+errors of both signs stay far below the first term alone."""
 import numpy as np
 import pytest
 import torch
